@@ -133,8 +133,8 @@ typedef enum { PIC_F32 = 0, PIC_F64 = 1 } pic_dtype_t;
 typedef struct {                /* [host] */
   int32_t abi_version;          /* == PIC_ABI_VERSION                                    */
   int32_t nx, ny;               /* mesh nodes per axis, 8 .. 1024 (any integer: mixed-
-                                   radix FFTs; powers of two take the compiled tile
-                                   geometries and are required by PIC_FLAG_ADJOINT)     */
+                                   radix FFTs; powers of two are required by
+                                   PIC_FLAG_ADJOINT)                                    */
   int32_t spline_degree;        /* 1 (linear), 2 (quadratic, the paper's), 3 (cubic),
                                    4, 5 (quartic, quintic; not with the adjoint)         */
   double lx, ly;                /* periodic box [0,lx) x [0,ly)                          */

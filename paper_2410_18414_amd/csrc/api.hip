@@ -943,8 +943,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   }
   c->sort_every = every;
   c->geo = tiled_geometry(c->inst[0].d.tp);
-  for (int i = 1; i < ninst; ++i)
-    if (tiled_geometry(c->inst[i].d.tp) != c->geo) c->geo = 0;
+  for (int i = 1; i < ninst; ++i) c->geo = common_geometry(c->geo, tiled_geometry(c->inst[i].d.tp));
   if (e != hipSuccess) {
     g_err = std::string("context setup: ") + hipGetErrorString(e);
     delete c;

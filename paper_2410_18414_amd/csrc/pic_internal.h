@@ -381,8 +381,10 @@ hipError_t launch_particle_diag(int dtype, const void* parts, int64_t n, PhysP p
 size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
 hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int nb_count, int nb_tiles, int nb_part,
                             int src_set, hipStream_t s);
-// geometry code of a tile plan: a compiled window shape (1, 2) or 0 (from TileP)
+// geometry code of a tile plan: a compiled window shape (1, 2: power-of-two
+// grids; 3, 4: any grid) or 0 (from TileP); the code two instances share
 int tiled_geometry(const TileP& tp);
+int common_geometry(int a, int b);
 hipError_t launch_tiled(int dtype, int mode, int degree, int geo, const InstDesc* D, int ninst, int nblocks,
                         size_t lds, StepArgs sa, hipStream_t s);
 
