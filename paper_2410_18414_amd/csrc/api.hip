@@ -213,13 +213,15 @@ TileP plan_tiles(const pic_config_t& c) {
   while (chunk < 4096 && c.max_particles / (2 * chunk) >= 8192) chunk *= 2;
   t.chunk = c.chunk ? c.chunk : chunk;
   t.max_work = t.ntiles + ceil_div(c.max_particles, t.chunk);
+  t.log_group = 0;
+  while ((t.ntiles - 1) >> t.log_group >= kMaxBuckets) t.log_group++;
   return t;
 }
 
 struct Layout {
   size_t set_bytes;  // one particle set: 11 arrays (cap x es) + ids
   size_t parts, J, T, RB, H, U, F64, F32, twx, twy, tcount, tstart, tcstart, ccount, ccursor, twork, tnwork, tdone,
-      trank,
+      trank, tbucket,
       LF, LS, LJ, LAM, LAM2, LIDS, LINV, LFLAG, total;
   size_t plane_c;    // complex entries per spectral plane
 };
@@ -264,6 +266,7 @@ Layout plan_instance(const pic_config_t& c) {
   L.tnwork = take(4);
   L.tdone = take(4);
   L.trank = take((size_t)cap * 4);
+  L.tbucket = take((size_t)2 * kMaxBuckets * 4);
   if (c.flags & PIC_FLAG_ADJOINT) {
     L.LF = take(11 * plane_r * 8);
     L.LS = take(11 * L.plane_c * 16);
@@ -496,6 +499,7 @@ struct pic_ctx_s {
   size_t lds_r2c = 0, lds_c2r = 0, lds_col = 0, lds_adj_col = 0, lds_tiled[3] = {0, 0, 0};
   int max_ny = 0;  // largest grid side in y over the instances (column kernel block size)
   int dtype = 0, degree = 3, scheme = 0;
+  int split_items = 0;  // particles per thread of the bucket split (first sort)
   int geo = 0;  // compiled window geometry shared by every instance (0: none, runtime geometry)
   bool sorted = true;
   int sort_every = 4;
@@ -614,16 +618,30 @@ struct pic_ctx_s {
 
 namespace {
 
+// particles from which on the reorderings through buckets are used (more
+// launches, but no scattered single values): float32 on 128 x 128, first sort
+// 60 us straight and 72 through buckets at 131072 particles, 82 and 79 at
+// 262144, 233 and 125 at 1M; export 41 and 55 us at 262144, 146 and 100 at 1M
+constexpr int64_t kFirstSortMin = 1 << 18, kExportMin = 1 << 19;
+
 // counting sort of every instance's particles by tile into the other set
 pic_status_t do_sort(pic_ctx_t c) {
   if (!c->sorted) return PIC_OK;
   auto* t = c->begin_timed(4);
-  hipError_t e = launch_tile_sort(c->dtype, c->d_desc, c->ninst(), c->nblk[BK_COUNT], c->nblk[BK_TILES],
-                                  c->nblk[BK_PART], c->cur, c->stream);
+  // particles in no known order go by way of tile buckets, back into their own
+  // set; a set that has been sorted before goes straight to the other one
+  int64_t n = 0;
+  for (const Instance& in : c->inst) n += in.d.n;
+  const bool first = !c->from_sort && n >= kFirstSortMin;
+  const hipError_t e =
+      first ? launch_first_sort(c->dtype, c->d_desc, c->ninst(), c->split_items, c->nblk[BK_SPLIT], c->nblk[BK_TILES],
+                                c->cur, c->stream)
+            : launch_tile_sort(c->dtype, c->d_desc, c->ninst(), c->nblk[BK_COUNT], c->nblk[BK_TILES],
+                               c->nblk[BK_PART], c->cur, c->stream);
   c->end_timed(t);
   pic_status_t st = c->hip(e, "tile sort");
   if (st) return st;
-  c->cur ^= 1;
+  if (!first) c->cur ^= 1;
   c->moves = 0;
   c->order_tag = new_order_tag();
   c->from_sort = true;
@@ -811,6 +829,9 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   c->d_desc = (InstDesc*)c->ws;
   c->d_diag = (double*)(c->ws + align_up(ninst * sizeof(InstDesc)));
   c->inst.resize(ninst);
+  int64_t cap = 0;
+  for (int i = 0; i < ninst; ++i) cap += cfgs[i].max_particles;
+  c->split_items = split_items(cap, c->dtype == PIC_F32 ? 4 : 8);
   size_t off = head_bytes(ninst);
   int every = 64;
   std::vector<double> tw;
@@ -862,6 +883,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     d.tb.nwork = (int32_t*)(b + in.L.tnwork);
     d.tb.done = (int32_t*)(b + in.L.tdone);
     d.tb.rank = (int32_t*)(b + in.L.trank);
+    d.tb.bcount = (int32_t*)(b + in.L.tbucket);
+    d.tb.bcursor = d.tb.bcount + kMaxBuckets;
     const bool adj = (cf.flags & PIC_FLAG_ADJOINT) != 0;
     d.LF = adj ? (double*)(b + in.L.LF) : nullptr;
     d.LS = adj ? (double2*)(b + in.L.LS) : nullptr;
@@ -910,7 +933,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
                                (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
                                ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
                                ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 1024),
-                               ceil_div(d.tp.ntiles, 4)};
+                               ceil_div(d.tp.ntiles, 4),
+                               ceil_div(cf.max_particles, kSplitWidth * c->split_items)};
     for (int k = 0; k < BK_NKINDS; ++k) {
       d.blk[k] = c->nblk[k];
       c->nblk[k] += nb[k];
@@ -940,6 +964,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     if (e == hipSuccess) e = hipMemset(d.tb.count, 0, (size_t)d.tp.ntiles * 4);
     if (e == hipSuccess) e = hipMemset(d.tb.ccount, 0, (size_t)d.tp.ntiles * d.tp.ts * d.tp.ts * 4);
     if (e == hipSuccess) e = hipMemset(d.tb.done, 0, 4);
+    if (e == hipSuccess) e = hipMemset(d.tb.bcount, 0, kMaxBuckets * 4);
   }
   c->sort_every = every;
   c->geo = tiled_geometry(c->inst[0].d.tp);
@@ -1304,6 +1329,11 @@ pic_status_t pic_get_particles(pic_ctx_t c, double* out) {
   if (c->phase == EMPTY) return c->fail(PIC_ERR_STATE, "no particles loaded");
   Instance& in = c->I();
   if (in.d.n > 0 && !out) return c->fail(PIC_ERR_INVALID_ARG, "out is NULL");
+  if (in.d.n >= kExportMin) {
+    // by way of the other particle set, which holds nothing between sorts
+    auto split = parts_of(c, in.d, c->cur ^ 1);
+    return c->hip(launch_export(c->dtype, c->d_desc, c->sel, in.d.n, c->cur, &split, out, c->stream), "get_particles");
+  }
   auto pa = parts_of(c, in.d, c->cur);
   return c->hip(launch_get_particles(c->dtype, &pa, in.d.n, out, c->stream), "get_particles");
 }

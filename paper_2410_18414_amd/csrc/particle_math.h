@@ -122,6 +122,24 @@ struct Spline {
   }
 };
 
+// cell key of a position (cells floor(xi), clamped into the grid), numbered
+// tile-major: tile * ts^2 + (row in tile) * ts + (column in tile)
+__device__ __forceinline__ int cell_of(float xi, float eta, const TileP& tp) {
+  int cx = (int)floorf(xi), cy = (int)floorf(eta);
+  cx = cx < 0 ? 0 : (cx >= tp.nx ? tp.nx - 1 : cx);
+  cy = cy < 0 ? 0 : (cy >= tp.ny ? tp.ny - 1 : cy);
+  const int tile = (cy >> tp.log_ts) * tp.ntx + (cx >> tp.log_ts);
+  const int m = tp.ts - 1;
+  return (tile << (2 * tp.log_ts)) + ((cy & m) << tp.log_ts) + (cx & m);
+}
+
+template <typename T>
+__device__ __forceinline__ int cell_key(T x, T y, const GridP& g, const TileP& tp) {
+  const float xi = (float)(x * T(g.inv_dx)), eta = (float)(y * T(g.inv_dy));
+  const bool ok = xi == xi && eta == eta;  // non-finite positions go to cell 0
+  return ok ? cell_of(xi, eta, tp) : 0;
+}
+
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
 // x in (-L, 2L) -> [0, L); a value that rounds to L is set to 0 (selects,

@@ -219,6 +219,7 @@ struct TileP {
   int chunk;       // max particles per workgroup
   int max_work;    // ntiles + ceil(capacity/chunk): bound on the chunk count
   int pow2;        // 1: nx and ny are powers of two (node indices wrap by masks)
+  int log_group;   // 2^log_group neighbouring tiles form a bucket of the first sort (at most kMaxBuckets)
 };
 
 // Window geometry: compile-time for the compiled tile shapes (TS > 0: tiles of
@@ -231,6 +232,11 @@ struct Geo {
   static constexpr int RL = W <= 8 ? 8 : (W <= 16 ? 16 : (W <= 32 ? 32 : 64));
   static constexpr int LRL = RL == 8 ? 3 : (RL == 16 ? 4 : (RL == 32 ? 5 : 6));
 };
+
+// Buckets of the reorderings (reorder.hip) and the threads per workgroup of
+// their split pass
+constexpr int kMaxBuckets = 1024;
+constexpr int kSplitWidth = 512;
 
 // Particles are counting-sorted by cell, cells numbered tile-major (the
 // ts*ts cells of tile t are keys t*ts*ts .. (t+1)*ts*ts - 1), so each tile's
@@ -246,6 +252,8 @@ struct TileBufs {
   int32_t* nwork;    // [1]        chunks in use
   int32_t* done;     // [1]        blocks of the cell scan finished; zero between sorts
   int32_t* rank;     // [capacity] each particle's slot among its cell's particles (count pass)
+  int32_t* bcount;   // [kMaxBuckets] particles per bucket; zero between uses
+  int32_t* bcursor;  // [kMaxBuckets] next free slot of each bucket
 };
 
 struct SchemeCoef {
@@ -275,7 +283,8 @@ enum BlockKind {
   BK_PART = 4,   // ceil(capacity/256) blocks (untiled passes, scatter)
   BK_COUNT = 5,  // ceil(capacity/1024) blocks (tile counting)
   BK_TILES = 6,  // ceil(ntiles/4) blocks (per-tile cell scan, one wave per tile)
-  BK_NKINDS = 7
+  BK_SPLIT = 7,  // ceil(capacity/(kSplitWidth split_items)) blocks (bucket split)
+  BK_NKINDS = 8
 };
 
 // One instance of the method: static for the life of a context.
@@ -381,6 +390,15 @@ hipError_t launch_particle_diag(int dtype, const void* parts, int64_t n, PhysP p
 size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
 hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int nb_count, int nb_tiles, int nb_part,
                             int src_set, hipStream_t s);
+hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s);
+// reorder.hip: the sort of sets in no known order (src -> src, by way of
+// src ^ 1, every instance), and one instance's set src to out in original order
+// (by way of the set src ^ 1, split_parts)
+int split_items(int64_t n, int es);  // particles per thread of the split pass for n particles in all
+hipError_t launch_first_sort(int dtype, const InstDesc* D, int ninst, int items, int nb_split, int nb_tiles, int src,
+                             hipStream_t s);
+hipError_t launch_export(int dtype, const InstDesc* D, int inst, int64_t n, int src, const void* split_parts,
+                         double* out, hipStream_t s);
 // geometry code of a tile plan: a compiled window shape (1, 2: power-of-two
 // grids; 3, 4: any grid) or 0 (from TileP); the code two instances share
 int tiled_geometry(const TileP& tp);

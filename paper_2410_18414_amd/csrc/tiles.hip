@@ -92,24 +92,6 @@ __device__ __forceinline__ void deposit_global_fixed(int sx, int sy, const T* wx
   }
 }
 
-// cell key of a position (cells floor(xi), clamped into the grid), numbered
-// tile-major: tile * ts^2 + (row in tile) * ts + (column in tile)
-__device__ __forceinline__ int cell_of(float xi, float eta, const TileP& tp) {
-  int cx = (int)floorf(xi), cy = (int)floorf(eta);
-  cx = cx < 0 ? 0 : (cx >= tp.nx ? tp.nx - 1 : cx);
-  cy = cy < 0 ? 0 : (cy >= tp.ny ? tp.ny - 1 : cy);
-  const int tile = (cy >> tp.log_ts) * tp.ntx + (cx >> tp.log_ts);
-  const int m = tp.ts - 1;
-  return (tile << (2 * tp.log_ts)) + ((cy & m) << tp.log_ts) + (cx & m);
-}
-
-template <typename T>
-__device__ __forceinline__ int cell_key(T x, T y, const GridP& g, const TileP& tp) {
-  const float xi = (float)(x * T(g.inv_dx)), eta = (float)(y * T(g.inv_dy));
-  const bool ok = xi == xi && eta == eta;  // non-finite positions go to cell 0
-  return ok ? cell_of(xi, eta, tp) : 0;
-}
-
 // The lanes of this lane's wave that hold the same key (0 for an inactive
 // lane): a ballot per distinct key of the wave (particles are nearly sorted
 // between sorts, so a wave holds few keys).
@@ -848,6 +830,11 @@ hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int nb_coun
     else
       hipLaunchKernelGGL(k_tile_scatter<double>, dim3(nb_part), dim3(kThreads), 0, s, D, ninst, src_set);
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s) {
+  hipLaunchKernelGGL(k_cell_scan, dim3(nb_tiles), dim3(kThreads), 0, s, D, ninst);
   return hipGetLastError();
 }
 
