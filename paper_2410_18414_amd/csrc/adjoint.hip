@@ -459,11 +459,11 @@ __global__ void __launch_bounds__(256) k_adj_columns(const InstDesc* __restrict_
   for (int f0 = 0; f0 < 11; f0 += NB) {
     const int nb = min(NB, 11 - f0);
     for (int t = threadIdx.x; t < nb * N; t += blockDim.x) {
-      const int qf = t / N, y = t - qf * N;
+      const int qf = fdiv(t, d.fy.inv_n), y = t - qf * N;
       wk[t] = LS[((size_t)(f0 + qf) * nxh + kx) * N + y];
     }
     __syncthreads();
-    const double2* res = fft_lds<false>(wk, wk + nb * N, N, nb, tws);
+    const double2* res = fft_lds<false>(wk, wk + nb * N, d.fy, nb, tws);
     // each thread owns its ky entries of acc: the field loop is serial
     for (int ky = threadIdx.x; ky < N; ky += blockDim.x) {
       const double kys = ky_sym(ky, g);
@@ -526,9 +526,9 @@ __global__ void __launch_bounds__(256) k_adj_columns(const InstDesc* __restrict_
     wk[2 * N + ky] = cscale(lJz, 1.0 / wgt);
   }
   __syncthreads();
-  const double2* res = fft_lds<true>(wk, wk + 3 * N, N, 3, tws);
+  const double2* res = fft_lds<true>(wk, wk + 3 * N, d.fy, 3, tws);
   for (int t = threadIdx.x; t < 3 * N; t += blockDim.x) {
-    const int c = t / N, y = t - c * N;
+    const int c = fdiv(t, d.fy.inv_n), y = t - c * N;
     LS[((size_t)c * nxh + kx) * N + y] = res[t];
   }
 }

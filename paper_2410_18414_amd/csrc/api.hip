@@ -874,6 +874,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     d.F32 = cf.particle_dtype == PIC_F32 ? (float*)(b + in.L.F32) : nullptr;
     d.twx = (const double2*)(b + in.L.twx);
     d.twy = (const double2*)(b + in.L.twy);
+    d.fx = plan_fft(cf.nx);
+    d.fy = plan_fft(cf.ny);
     d.tb.count = (int32_t*)(b + in.L.tcount);
     d.tb.start = (int32_t*)(b + in.L.tstart);
     d.tb.ccount = (int32_t*)(b + in.L.ccount);

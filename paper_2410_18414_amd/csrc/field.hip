@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 namespace pic {
 
@@ -53,13 +54,13 @@ __global__ void __launch_bounds__(256) k_rows_r2c(const InstDesc* __restrict__ D
   const gptr<const double> reset = gp((const double*)((!adj && c == 3) ? d.RB : nullptr));
   const bool det = !adj && d.det;
   const GC2 T = gc2(adj ? d.LS : d.T);
-  const int N = g.nx, B = R >> 1;
+  const int N = g.nx, B = R >> 1, lR = __ffs(R) - 1;  // R: a power of two
   double2* a = sm;
   double2* b = sm + B * N;
   double2* tws = sm + R * N;  // twiddles staged in LDS
   for (int t = threadIdx.x; t < N; t += blockDim.x) tws[t] = gc2(d.twx)[t];
   for (int t = threadIdx.x; t < B * N; t += blockDim.x) {
-    const int r = t / N, x = t - r * N;
+    const int r = fdiv(t, d.fx.inv_n), x = t - r * N;
     const size_t i0 = (size_t)(y0 + 2 * r) * N + x, i1 = i0 + N;
     const bool h0 = 2 * r < nr, h1 = 2 * r + 1 < nr;
     if (det) {  // deterministic deposit: int64 sums at scale 2^qe_det
@@ -73,10 +74,10 @@ __global__ void __launch_bounds__(256) k_rows_r2c(const InstDesc* __restrict__ D
     if (h1) Jc[i1] = reset ? reset[i1] : 0.0;
   }
   __syncthreads();
-  const double2* res = fft_lds<false>(a, b, N, B, tws);
+  const double2* res = fft_lds<false>(a, b, d.fx, B, tws);
   // split the two real transforms: X = (Z_k + conj Z_{N-k})/2, Y = (Z_k - conj Z_{N-k})/(2i)
   for (int t = threadIdx.x; t < g.nxh * R; t += blockDim.x) {
-    const int k = t / R, rr = t - k * R, r = rr >> 1;
+    const int k = t >> lR, rr = t & (R - 1), r = rr >> 1;
     if (rr >= nr) continue;
     const double2 zk = res[r * N + k];
     const double2 zn = cconj(res[r * N + (k ? N - k : 0)]);
@@ -106,8 +107,8 @@ __global__ void __launch_bounds__(256) k_rows_r2c(const InstDesc* __restrict__ D
 constexpr int kColParts = 4;
 constexpr int kMaxStages = 3;  // DIRK stages: loops over them unrolled to this bound (registers, not scratch)
 // modes per thread: 256 threads up to ny = 512, 512 threads above (ny <= 1024);
-// two modes keep the DIRK update's per-mode values within a register budget
-// that admits three waves per SIMD
+// with two modes the DIRK update's per-mode values stay in registers (229 VGPRs;
+// a bound of three waves per SIMD spills and is 5 us slower at 128 x 128)
 constexpr int kColMaxModes = 2;
 
 template <int SCHEME, int K>
@@ -147,7 +148,7 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
   const int ncol = part == 0 && !naive_rho ? 2 : 1;
   const int c0 = part == 0 ? (naive_rho ? 3 : 0) : part - 1;
   for (int i = tid; i < ncol * N; i += nth) {
-    const int c = i / N, y = i - c * N;
+    const int c = i >= N, y = c ? i - N : i;
     wk[i] = T[((size_t)(c0 + c) * g.nxh + kx) * N + y];
   }
   // history terms of this thread's modes ky = tid + m * nth
@@ -206,18 +207,18 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
     for (int st = 0; st < nst; ++st) {
       if (st > 0) {
         for (int i = tid; i < ncol * N; i += nth) {
-          const int c = i / N, y = i - c * N;
+          const int c = i >= N, y = c ? i - N : i;
           wk[i] = T[((size_t)(3 * st + c0 + c) * g.nxh + kx) * N + y];
         }
         __syncthreads();
       }
-      const double2* r = fft_lds<false>(wk, wk + 2 * N, N, ncol, tws);
+      const double2* r = fft_lds<false>(wk, wk + 2 * N, d.fy, ncol, tws);
       for (int i = tid; i < ncol * N; i += nth) stg[st * ncol * N + i] = r[i];
       __syncthreads();
     }
     Jh = stg;
   } else {
-    Jh = fft_lds<false>(wk, wk + 2 * N, N, ncol, tws);
+    Jh = fft_lds<false>(wk, wk + 2 * N, d.fy, ncol, tws);
   }
   const double kxs = kx_sym(kx, g);
   const double scale = 1.0 / ((double)g.nx * g.ny);
@@ -386,15 +387,15 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
   __syncthreads();
   // outputs: the field and its y derivative (G0, G1 or G(2+l), G(5+l))
   for (int i = tid; i < 2 * N; i += nth) {
-    const int q = i / N, ky = i - q * N;
+    const int q = i >= N, ky = q ? i - N : i;
     const double2 v = store[ky];
     wk[i] = q ? mul_i(cscale(v, ky_sym(ky, g))) : v;
   }
   __syncthreads();
-  const double2* res = fft_lds<true>(wk, wk + 2 * N, N, 2, tws);
+  const double2* res = fft_lds<true>(wk, wk + 2 * N, d.fy, 2, tws);
   const int g0 = part == 0 ? 0 : 2 + c0, g1 = part == 0 ? 1 : 5 + c0;
   for (int i = tid; i < 2 * N; i += nth) {
-    const int q = i / N, y = i - q * N;
+    const int q = i >= N, y = q ? i - N : i;
     U[((size_t)(q ? g1 : g0) * g.nxh + kx) * N + y] = res[i];
   }
 }
@@ -425,7 +426,7 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
   const int ii = find_inst(D, ninst, BK_C2R, bb);
   const InstDesc& d = D[ii];
   const GridP g = d.g;
-  const int R = d.R_c2r;
+  const int R = d.R_c2r, lR = __ffs(R) - 1;  // a power of two
   const int np = adj ? 2 : 6;  // output pairs per row group
   const int lb = bb - d.blk[BK_C2R];
   const int rg = lb / np, pr = lb - rg * np, y0 = rg * R;
@@ -443,7 +444,7 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
   const int g0 = adj ? s0 : kSrcG[s0], g1 = adj ? s1 : kSrcG[s1];
   const bool has1 = !adj || s1 < 3;
   for (int t = threadIdx.x; t < g.nxh * R; t += blockDim.x) {
-    const int k = t / R, r = t - k * R;
+    const int k = t >> lR, r = t & (R - 1);
     if (r >= nr) {  // past the last row: zero input, output not written
       a[r * N + k] = make_double2(0.0, 0.0);
       if (k > 0 && k != nyq) a[r * N + N - k] = make_double2(0.0, 0.0);
@@ -463,10 +464,10 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
     if (k > 0 && k != nyq) a[r * N + N - k] = cadd(cconj(X), mul_i(cconj(Y)));
   }
   __syncthreads();
-  const double2* res = fft_lds<true>(a, b, N, R, tws);
+  const double2* res = fft_lds<true>(a, b, d.fx, R, tws);
   const size_t plane = (size_t)g.nx * g.ny;
   for (int t = threadIdx.x; t < nr * N; t += blockDim.x) {
-    const int r = t / N, x = t - r * N;
+    const int r = fdiv(t, d.fx.inv_n), x = t - r * N;
     const size_t o = (size_t)(y0 + r) * N + x;
     const double2 z = res[t];
     if (f64out || !F32) {
@@ -628,6 +629,28 @@ void fft_make_twiddles(int n, double* h) {
     h[2 * t] = (double)cosl(ang);
     h[2 * t + 1] = (double)(-sinl(ang));
   }
+}
+
+// Radices of an FFT length: odd primes first, the largest first (the earlier a
+// pass, the fewer twiddles it has), then 4 and a last 2
+FftPlan plan_fft(int n) {
+  FftPlan p{};
+  p.n = n;
+  p.inv_n = 1.0f / n;
+  int rem = n, l2 = 0;
+  while (rem % 2 == 0) {
+    rem /= 2;
+    ++l2;
+  }
+  std::vector<int> r;
+  for (int f = 3; rem > 1; f += 2)
+    while (rem % f == 0) {
+      r.insert(r.begin(), f);
+      rem /= f;
+    }
+  for (; l2 > 0; l2 -= 2) r.push_back(l2 >= 2 ? 4 : 2);
+  for (size_t i = 0; i < r.size(); ++i) p.radices[i / 4] |= (uint64_t)r[i] << (16 * (i % 4));
+  return p;
 }
 
 // rows per block of the row kernels: at most 8, within the LDS budget, and

@@ -274,6 +274,22 @@ struct SchemeCoef {
 // (three 16-byte vectors), the layout of the tiled passes' LDS windows.
 constexpr int kFieldSlots = 12;
 
+// One FFT length (fft_lds.h): its passes' radices in order, 16 bits each (at
+// most eight passes; powers of two choose their own)
+struct FftPlan {
+  int n;
+  float inv_n;  // 1 / n
+  uint64_t radices[2];
+};
+FftPlan plan_fft(int n);
+// t / n for 0 <= t < 2^21 from 1 / n, also the hardware's (a 32-bit division is
+// some forty instructions)
+__device__ __forceinline__ int fdiv(int t, float inv_n) { return (int)(((float)t + 0.5f) * inv_n); }
+// a / b of wave-uniform numbers below 2^21, a divisible by b, in scalar registers
+__device__ __forceinline__ int udiv_exact(int a, int b) {
+  return __builtin_amdgcn_readfirstlane((int)((float)a * __builtin_amdgcn_rcpf((float)b) + 0.5f));
+}
+
 // block ranges of the flattened kernels
 enum BlockKind {
   BK_R2C = 0,    // (ny/R_r2c) x 3 blocks
@@ -303,6 +319,7 @@ struct InstDesc {
   float* F32;
   const double2* twx;
   const double2* twy;
+  FftPlan fx, fy;           // transforms along x and y
   double* LF;               // adjoint buffers (PIC_FLAG_ADJOINT, else null): [11][ny][nx] mesh-field adjoints,
   double2* LS;              // [11][nxh][ny] their x-transforms (planes 0..2 reused for the J adjoint columns),
   double* LJ;               // [3][ny][nx] adjoint of J,
