@@ -177,10 +177,72 @@ bool compatible(const pic_config_t& a, const pic_config_t& b, std::string& msg) 
   return true;
 }
 
+// Particles per chunk (workgroup) of the sorted passes, where the config leaves
+// them open: the candidate of least modelled time of the fused pass for
+// uniformly placed particles.  A tile's chunks have equal sizes.  A workgroup
+// costs its window load and flush, about 1.2 iterations of its 256 lanes, and
+// its iterations, a partly filled one nearly as much as a full one; the chip
+// holds `slots` workgroups (by LDS four float32 or two float64 ones per CU), and
+// about half a workgroup's time passes before the last ones end.  Measured
+// (fused pass, us, by particles per chunk): 128 x 128 with 1M float32 particles
+// 497: 33.0, 512 and a few: 35.6, 683: 32.2, 964: 33.2; float64 497: 70, 1024:
+// 64, 1365: 61, 2048: 60, 2731: 73; 256 x 256 with 2M float32 482: 46, 512 and a
+// few: 53, 683: 44.6, 910: 43.7; 64 x 64 with 32768 float64 256: 10.6, 512: 13.5.
+// Float32 candidates stay below twice the power of two (512 .. 4096, the largest
+// that leaves 8192 chunks) that fixes the deposit's scale.  Sets of at most 8192
+// particles take chunks of 128 (9.4 us instead of 13.2 with 4096 particles).
+// An instance of an ensemble has its share (by particles, total) of the slots.
+int chunk_base(int64_t n) {
+  int base = 512;
+  while (base < 4096 && n / (2 * base) >= 8192) base *= 2;
+  return base;
+}
+int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
+  const int64_t n = c.max_particles;
+  const int base = chunk_base(n);
+  const bool f32 = c.particle_dtype == PIC_F32;
+  if (n <= 8192) return 128;
+  const size_t lds = tiled_lds_bytes(c.particle_dtype, 2, t, (c.flags & PIC_FLAG_NAIVE_RHO) != 0);
+  const double per_cu = (double)std::max<size_t>(1, std::min<size_t>(4, 163840 / lds));
+  const double slots = 256.0 * per_cu * ((double)n / (double)total);
+  // tiles by extent (full, and partial at the high edges), with four standard
+  // deviations of margin on their expected particles
+  const int fx = c.nx / t.ts, fy = c.ny / t.ts, rx = c.nx - fx * t.ts, ry = c.ny - fy * t.ts;
+  const double per_cell = (double)n / ((double)c.nx * c.ny);
+  const double tiles[4][2] = {{(double)fx * fy, per_cell * t.ts * t.ts},
+                              {rx ? (double)fy : 0.0, per_cell * rx * t.ts},
+                              {ry ? (double)fx : 0.0, per_cell * ry * t.ts},
+                              {rx && ry ? 1.0 : 0.0, per_cell * rx * ry}};
+  int best = base;
+  double best_cost = 1e300;
+  for (int chunk = 256; chunk < (f32 ? 2 * base : 8192); chunk += 16) {
+    double items = 0.0, iters = 0.0;
+    for (const auto& k : tiles) {
+      if (k[0] == 0.0) continue;
+      const double parts = std::ceil((k[1] + 4.0 * std::sqrt(k[1])) / chunk);
+      items += k[0] * parts;
+      const double size = k[1] / parts + std::sqrt(k[1]) / parts, whole = std::floor(size / 256.0);
+      const double part = size / 256.0 - whole;
+      iters = std::max(iters, whole + (part > 0.0 ? std::max(0.7, part) : 0.0));
+    }
+    // fewer workgroups than CUs: an iteration has the CU's units to itself
+    const double load = n == total ? std::max(0.4, std::min(1.0, std::ceil(items / 256.0) / per_cu)) : 1.0;
+    // rounds: workgroups start as others end, so a partial round costs more than
+    // its share and less than a whole one
+    const double share = items / slots, rounds = n == total ? 0.5 * (share + std::ceil(share)) : share;
+    const double cost = (std::max(1.0, rounds) + 0.5) * (1.2 + load * iters);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = chunk;
+    }
+  }
+  return best;
+}
+
 // Tile plan: tiles of 16x16 cells (smaller on small grids), a slack of three
-// cells, chunks of at most 512 particles per workgroup, unless the config
-// sets them.
-TileP plan_tiles(const pic_config_t& c) {
+// cells, chunks by plan_chunk, unless the config sets them.  total: the
+// capacity of all instances of the context.
+TileP plan_tiles(const pic_config_t& c, int64_t total) {
   TileP t{};
   t.nx = c.nx;
   t.ny = c.ny;
@@ -206,12 +268,7 @@ TileP plan_tiles(const pic_config_t& c) {
     t.row_lanes <<= 1;
     t.log_row_lanes += 1;
   }
-  // default chunk: the largest of 512 .. 4096 particles that still leaves
-  // at least 8192 chunks (32 per CU) at full capacity; bigger chunks amortise
-  // the window load and flush once parallelism is plentiful
-  int chunk = 512;
-  while (chunk < 4096 && c.max_particles / (2 * chunk) >= 8192) chunk *= 2;
-  t.chunk = c.chunk ? c.chunk : chunk;
+  t.chunk = c.chunk ? c.chunk : plan_chunk(c, t, total);
   t.max_work = t.ntiles + ceil_div(c.max_particles, t.chunk);
   t.log_group = 0;
   while ((t.ntiles - 1) >> t.log_group >= kMaxBuckets) t.log_group++;
@@ -221,14 +278,14 @@ TileP plan_tiles(const pic_config_t& c) {
 struct Layout {
   size_t set_bytes;  // one particle set: 11 arrays (cap x es) + ids
   size_t parts, J, T, RB, H, U, F64, F32, twx, twy, tcount, tstart, tcstart, ccount, ccursor, twork, tnwork, tdone,
-      trank, tbucket,
+      trank, tbucket, tcsize,
       LF, LS, LJ, LAM, LAM2, LIDS, LINV, LFLAG, total;
   size_t plane_c;    // complex entries per spectral plane
 };
 
 SchemeCoef make_scheme(const pic_config_t& c);
 
-Layout plan_instance(const pic_config_t& c) {
+Layout plan_instance(const pic_config_t& c, int64_t total) {
   Layout L{};
   const size_t es = c.particle_dtype == PIC_F32 ? 4 : 8;
   const size_t cap = (size_t)c.max_particles;
@@ -236,7 +293,7 @@ Layout plan_instance(const pic_config_t& c) {
   const size_t plane_r = (size_t)c.nx * c.ny;
   L.plane_c = nxh * c.ny;
   const Hist h = plan_history(c);
-  const TileP tp = plan_tiles(c);
+  const TileP tp = plan_tiles(c, total);
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -259,6 +316,7 @@ Layout plan_instance(const pic_config_t& c) {
   L.tcount = take((size_t)tp.ntiles * 4);
   L.tstart = take(((size_t)tp.ntiles + 1) * 4);
   L.tcstart = take((size_t)tp.ntiles * 4);
+  L.tcsize = take((size_t)tp.ntiles * 4);
   const size_t ckeys = (size_t)tp.ntiles * tp.ts * tp.ts;  // cell keys (>= nx ny)
   L.ccount = take(ckeys * 4);
   L.ccursor = take(ckeys * 4);
@@ -287,9 +345,15 @@ Layout plan_instance(const pic_config_t& c) {
 constexpr size_t kDiagDoubles = 16 + 2 * 256;
 size_t head_bytes(int ninst) { return align_up(ninst * sizeof(InstDesc)) + align_up(kDiagDoubles * 8); }
 
+int64_t total_capacity(const pic_config_t* cfgs, int ninst) {
+  int64_t n = 0;
+  for (int i = 0; i < ninst; ++i) n += cfgs[i].max_particles;
+  return n;
+}
+
 size_t total_bytes(const pic_config_t* cfgs, int ninst) {
   size_t t = head_bytes(ninst);
-  for (int i = 0; i < ninst; ++i) t += plan_instance(cfgs[i]).total;
+  for (int i = 0; i < ninst; ++i) t += plan_instance(cfgs[i], total_capacity(cfgs, ninst)).total;
   return t;
 }
 
@@ -829,8 +893,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   c->d_desc = (InstDesc*)c->ws;
   c->d_diag = (double*)(c->ws + align_up(ninst * sizeof(InstDesc)));
   c->inst.resize(ninst);
-  int64_t cap = 0;
-  for (int i = 0; i < ninst; ++i) cap += cfgs[i].max_particles;
+  const int64_t cap = total_capacity(cfgs, ninst);
   c->split_items = split_items(cap, c->dtype == PIC_F32 ? 4 : 8);
   size_t off = head_bytes(ninst);
   int every = 64;
@@ -840,7 +903,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     Instance& in = c->inst[i];
     const pic_config_t& cf = cfgs[i];
     in.cfg = cf;
-    in.L = plan_instance(cf);
+    in.L = plan_instance(cf, cap);
     in.off = off;
     off += in.L.total;
     char* b = c->ws + in.off;
@@ -857,7 +920,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     g.inv_dy = 1.0 / g.dy;
     g.inv_area = 1.0 / (g.dx * g.dy);
     d.ph = PhysP{cf.dt, cf.q, cf.m, cf.c};
-    d.tp = plan_tiles(cf);
+    d.tp = plan_tiles(cf, cap);
     d.sc = make_scheme(cf);
     const size_t es = cf.particle_dtype == PIC_F32 ? 4 : 8;
     const size_t cb = array_bytes((size_t)cf.max_particles, es);
@@ -882,6 +945,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     d.tb.ccursor = (int32_t*)(b + in.L.ccursor);
     d.tb.work = (int4*)(b + in.L.twork);
     d.tb.cstart = (int32_t*)(b + in.L.tcstart);
+    d.tb.csize = (int32_t*)(b + in.L.tcsize);
     d.tb.nwork = (int32_t*)(b + in.L.tnwork);
     d.tb.done = (int32_t*)(b + in.L.tdone);
     d.tb.rank = (int32_t*)(b + in.L.trank);
@@ -912,12 +976,12 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
       if (ok) std::frexp(B, &p);
       d.qe0 = ok ? 30 - p : 0;
       // deterministic deposit: one scale for every contribution of the
-      // instance.  Float32: the window scale of a full chunk (a chunk's sum
-      // below 2^30, so int64 sums of every chunk cannot overflow).  Float64:
+      // instance.  Float32: the window scale of a full chunk, whichever default
+      // size was planned (a chunk's sum below 2^31).  Float64:
       // capacity x B 2^e < 2^62 bounds every int64 sum, window or global.
       d.det = (cf.flags & PIC_FLAG_DETERMINISTIC) ? 1 : 0;
-      int cl2_chunk = 0, cl2_cap = 0;
-      while ((1 << cl2_chunk) < d.tp.chunk) ++cl2_chunk;
+      const int cl2_chunk = log2_sum(cf.chunk ? cf.chunk : chunk_base(cf.max_particles));
+      int cl2_cap = 0;
       while (((int64_t)1 << cl2_cap) < cf.max_particles) ++cl2_cap;
       int e = cf.particle_dtype == PIC_F32 ? d.qe0 - std::max(cl2_chunk, 9) : (ok ? 62 - p - cl2_cap : 0);
       e = cf.particle_dtype == PIC_F32 ? std::max(-100, std::min(100, e)) : std::max(-1000, std::min(1000, e));

@@ -233,6 +233,17 @@ struct Geo {
   static constexpr int LRL = RL == 8 ? 3 : (RL == 16 ? 4 : (RL == 32 ? 5 : 6));
 };
 
+// The fixed-point deposit's sums of `count` contributions, each below 2^21 at a
+// scale of qe0 - max(log2_sum, 9), stay below 2^31: with l = floor(log2(count)),
+// count B 2^(qe0 - l) < 2^(l + 1) 2^(30 - l), and the half unit each contribution
+// is rounded by fits below 2^31 while count < 2^14 (above that the next power
+// of two is taken).
+__host__ __device__ inline int log2_sum(int count) {
+  int l = 0;
+  while ((count >> l) > 1) ++l;
+  return count >= 16384 && (count & (count - 1)) ? l + 1 : l;
+}
+
 // Buckets of the reorderings (reorder.hip) and the threads per workgroup of
 // their split pass
 constexpr int kMaxBuckets = 1024;
@@ -249,6 +260,7 @@ struct TileBufs {
   int4* work;        // [max_work] (tile, first particle, count, rows): rows = r0 | r1 << 16, the
                      //            tile-local cell rows of the chunk's first and last particle at the sort
   int32_t* cstart;   // [ntiles]   each tile's first chunk in work
+  int32_t* csize;    // [ntiles]   particles per chunk of the tile (its last chunk may have fewer)
   int32_t* nwork;    // [1]        chunks in use
   int32_t* done;     // [1]        blocks of the cell scan finished; zero between sorts
   int32_t* rank;     // [capacity] each particle's slot among its cell's particles (count pass)

@@ -228,9 +228,10 @@ __global__ void __launch_bounds__(kSplitThreads) k_split(const InstDesc* __restr
     if (BY == BY_CELL) {
       // a chunk's first and last particles record its span of cell rows, as in the sort's scatter
       const int tt = c >> tile_bits, t0 = start[tt], rel = o - t0;
-      const int jc = rel / tp.chunk, in_chunk = rel - jc * tp.chunk;
+      const int sz = gp((const int32_t*)d.tb.csize)[tt];
+      const int jc = (int)((uint32_t)rel / (uint32_t)sz), in_chunk = rel - jc * sz;
       const bool fst = in_chunk == 0;
-      const bool lst = in_chunk == tp.chunk - 1 || rel == start[tt + 1] - t0 - 1;
+      const bool lst = in_chunk == sz - 1 || rel == start[tt + 1] - t0 - 1;
       if (fst || lst) {
         const int row = (c & ((1 << tile_bits) - 1)) >> tp.log_ts;
         const gptr<int> rows = gp(reinterpret_cast<int*>(d.tb.work + d.tb.cstart[tt] + jc) + 3);

@@ -186,9 +186,13 @@ __device__ void tile_scan_block(const InstDesc& d, const TileP& tp) {
     if (t < tp.ntiles) {
       d.tb.start[t] = p0;
       d.tb.cstart[t] = k0;
+      // the tile's k chunks have the same size (but the last): a small remainder
+      // chunk would cost a workgroup its window load and flush
+      const int sz = k ? (c + k - 1) / k : 1;
+      d.tb.csize[t] = sz;
       for (int j = 0; j < k; ++j) {
-        const int s = p0 + j * tp.chunk;
-        const int e = min(p0 + c, s + tp.chunk);
+        const int s = p0 + j * sz;
+        const int e = min(p0 + c, s + sz);
         d.tb.work[k0 + j] = make_int4(t, s, e - s, 0);
       }
     }
@@ -285,9 +289,10 @@ __global__ void __launch_bounds__(kThreads) k_tile_scatter(const InstDesc* __res
   // a chunk's first and last particles record its span of cell rows (slots
   // are in cell order, cells row-major in the tile) for the tiled pass's
   // field-window rows; the cell scan wrote the field as zero
-  const int j = rel / tp.chunk, in_chunk = rel - j * tp.chunk;
+  const int sz = gp((const int32_t*)d.tb.csize)[tt];
+  const int j = (int)((uint32_t)rel / (uint32_t)sz), in_chunk = rel - j * sz;
   const bool first = in_chunk == 0;
-  const bool last = in_chunk == tp.chunk - 1 || rel == start[tt + 1] - t0 - 1;
+  const bool last = in_chunk == sz - 1 || rel == start[tt + 1] - t0 - 1;
   if (first || last) {
     const int row = (c & ((1 << (2 * tp.log_ts)) - 1)) >> tp.log_ts;
     const gptr<int> rows = gp(reinterpret_cast<int*>(d.tb.work + d.tb.cstart[tt] + j) + 3);
@@ -480,8 +485,8 @@ __global__ void __launch_bounds__(kThreads) k_tiled(const InstDesc* __restrict__
   // per node instead of three float64 ones).  The scale is a power of two
   // 2^e chosen per chunk: every contribution is bounded by B = |q| c max(w) /
   // (dx dy) (|v| < c; 3c for |2 v - v_prev|), and B 2^qe0 < 2^30 (qe0 from the
-  // host, d.qe0), so with e = qe0 - max(ceil(log2 count), 9) a node's sum over
-  // the chunk stays below 2^30 (each packed half decodes for |sum| < 2^31) and
+  // host, d.qe0), so with e = qe0 - max(log2_sum(count), 9) a node's sum over
+  // the chunk stays below 2^31, where each packed half still decodes, and
   // a single contribution below 2^21 (the rounding FMA needs below 2^22).
   unsigned long long* jxy_w = reinterpret_cast<unsigned long long*>(jw);     // [JWP]
   uint32_t* jz_w = reinterpret_cast<uint32_t*>(jw + JWP);                      // [JWP]
@@ -489,7 +494,7 @@ __global__ void __launch_bounds__(kThreads) k_tiled(const InstDesc* __restrict__
   float qscale = 1.0f;
   double inv_qscale = 1.0;
   if (FIXEDPT) {
-    const int lz = it.z > 1 ? 32 - __clz(it.z - 1) : 0;  // ceil(log2 count)
+    const int l0 = 31 - __clz(max(it.z, 1)), lz = it.z >= 16384 && (it.z & (it.z - 1)) ? l0 + 1 : l0;  // log2_sum
     // deterministic deposit: the instance's fixed scale (that of a full chunk)
     int e = det ? d.qe_det : d.qe0 - (lz > 9 ? lz : 9);
     e = e > 100 ? 100 : (e < -100 ? -100 : e);  // a normal float scale, whatever q, c and the cell area
