@@ -311,8 +311,8 @@ pic_status_t pic_set_dirk_tableau(pic_ctx_t ctx, int32_t stages, const double* A
  * is allocated and no host buffer is touched (results are valid once the
  * stream has synchronised; a non-finite particle shows in out[i*8 + 7], and
  * the call itself returns PIC_OK).  The reduction partials live in a fixed
- * scratch array of the library, PIC_DIAG_ALL_MAX instances x 528 doubles
- * (270 KB), one copy per GPU the library runs on, held until the process
+ * scratch array of the library, PIC_DIAG_ALL_MAX instances x 1024 doubles
+ * (512 KB), one copy per GPU the library runs on, held until the process
  * ends; contexts with more instances get PIC_ERR_INVALID_ARG.  Every call on
  * one GPU shares that GPU's scratch: calls that overlap in time on one GPU
  * (from two streams or two host threads) race and may return each other's

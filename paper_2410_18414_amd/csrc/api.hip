@@ -339,11 +339,9 @@ Layout plan_instance(const pic_config_t& c, int64_t total) {
   return L;
 }
 
-// context-level buffers ahead of the instances: descriptors and diagnostics
-// diagnostics buffer: the field reduction's six values (16 slots), then 256
-// block partials of the kinetic energy and the non-finite count
-constexpr size_t kDiagDoubles = 16 + 2 * 256;
-size_t head_bytes(int ninst) { return align_up(ninst * sizeof(InstDesc)) + align_up(kDiagDoubles * 8); }
+// context-level buffers ahead of the instances: descriptors, and the word the
+// loading's largest speed is found in
+size_t head_bytes(int ninst) { return align_up(ninst * sizeof(InstDesc)) + kAlign; }
 
 int64_t total_capacity(const pic_config_t* cfgs, int ninst) {
   int64_t n = 0;
@@ -432,13 +430,12 @@ struct Instance {
 }  // namespace
 
 // ---------------------------------------------------------------------------
-// Scratch of pic_diagnostics_all: the per-instance reduction partials (the
-// field reduction's six values, then 256 block partials of the kinetic energy
-// and the non-finite count) of at most kDiagAllMax instances, in a
-// file-scope device array.  Each GPU the library runs on holds its own copy
-// until the process ends.  In host code the array's name is not a device
-// address: host code uses only the address hipGetSymbolAddress returns for
-// the current device, looked up once per device (scratch_on).
+// Scratch of pic_diagnostics_all: the block partials (kDiagDoubles) of at most
+// kDiagAllMax instances, in a file-scope device array.  Each GPU the library
+// runs on holds its own copy until the process ends.  In host code the array's
+// name is not a device address: host code uses only the address
+// hipGetSymbolAddress returns for the current device, looked up once per device
+// (scratch_on).
 constexpr int kDiagAllMax = 64;
 static __device__ __align__(256) double scratch[kDiagAllMax * kDiagDoubles];
 
@@ -458,23 +455,6 @@ double* scratch_on(int dev) {
     g_scratch[dev] = static_cast<double*>(ptr);
   }
   return g_scratch[dev];
-}
-
-// out[i][0..5] = instance i's field values, out[i][6] = its kinetic energy,
-// out[i][7] = its non-finite count: the block partials summed in block order,
-// as pic_diagnostics sums them on the host
-__global__ void k_diag_finalize(const double* __restrict__ part, int ninst, double* __restrict__ out) {
-  const int i = blockIdx.x;
-  if (i >= ninst || threadIdx.x != 0) return;
-  const double* p = part + (size_t)i * kDiagDoubles;
-  for (int k = 0; k < 6; ++k) out[i * PIC_DIAG_COUNT + k] = p[k];
-  double ke = 0, bad = 0;
-  for (int b = 0; b < 256; ++b) {
-    ke += p[16 + 2 * b];
-    bad += p[16 + 2 * b + 1];
-  }
-  out[i * PIC_DIAG_COUNT + 6] = ke;
-  out[i * PIC_DIAG_COUNT + 7] = bad;
 }
 
 }  // namespace
@@ -501,6 +481,15 @@ __global__ void k_state_header(int64_t* h, HeaderWords hw, int count) {
   if ((int)threadIdx.x < count) h[threadIdx.x] = hw.w[threadIdx.x];
 }
 
+// header words the first copy of a save writes too (a single-instance state has
+// 17: the one beyond them is in `last`)
+struct CopyHeader {
+  int64_t* dst;
+  HeaderWords hw;
+  int64_t last;
+  int count;
+};
+
 // copy every segment of the list: each workgroup copies one span of
 // kCopySpan bytes of one segment (the segment found by a wave-uniform scan of
 // the block prefix sums), every thread kCopyUnroll 16-byte vectors in flight;
@@ -517,8 +506,10 @@ struct CopyList {
   uint64_t bytes[kCopyMax];
 };
 
-__global__ void __launch_bounds__(kCopyThreads) k_copy_list(CopyList L) {
+__global__ void __launch_bounds__(kCopyThreads) k_copy_list(CopyList L, CopyHeader H) {
   const uint64_t b = blockIdx.x;
+  if (b == 0 && (int)threadIdx.x < H.count)
+    H.dst[threadIdx.x] = threadIdx.x < kStateHeaderWords ? H.hw.w[threadIdx.x] : H.last;
   int sg = 0;
   while (sg + 1 < L.count && L.first[sg + 1] <= b) ++sg;
   const uint64_t base = (b - L.first[sg]) * kCopySpan;
@@ -557,7 +548,8 @@ struct pic_ctx_s {
   char* ws = nullptr;
   Hist hist{};
   InstDesc* d_desc = nullptr;
-  double* d_diag = nullptr;
+  uint32_t* d_vmax = nullptr;
+  double* h_diag = nullptr;  // pinned: pic_diagnostics' kernels write their partials to it (first call allocates)
   double* d_scratch = nullptr;  // scratch's address on the context's device
   int nblk[BK_NKINDS] = {0};
   size_t lds_r2c = 0, lds_c2r = 0, lds_col = 0, lds_adj_col = 0, lds_tiled[3] = {0, 0, 0};
@@ -614,6 +606,7 @@ struct pic_ctx_s {
   double t_n[PIC_KCLASS_COUNT] = {0};
 
   ~pic_ctx_s() {
+    if (h_diag) (void)hipHostFree(h_diag);
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
     if (side) (void)hipStreamDestroy(side);
@@ -891,7 +884,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   c->scheme = scheme_family(cfgs[0].scheme);
   c->sorted = (cfgs[0].flags & PIC_FLAG_NO_SORT) == 0;
   c->d_desc = (InstDesc*)c->ws;
-  c->d_diag = (double*)(c->ws + align_up(ninst * sizeof(InstDesc)));
+  c->d_vmax = (uint32_t*)(c->ws + align_up(ninst * sizeof(InstDesc)));
   c->inst.resize(ninst);
   const int64_t cap = total_capacity(cfgs, ninst);
   c->split_items = split_items(cap, c->dtype == PIC_F32 ? 4 : 8);
@@ -1083,15 +1076,10 @@ std::vector<int> export_slots(pic_ctx_t c) {
 pic_status_t history_io(pic_ctx_t c, double* ext, bool to_external) {
   const std::vector<int> slots = export_slots(c);
   Instance& in = c->I();
-  const size_t plane = in.L.plane_c;
-  for (size_t f = 0; f < slots.size(); ++f) {
-    double2* in_slot = in.d.H + (size_t)slots[f] * plane;
-    double2* ext_f = (double2*)ext + f * plane;
-    hipError_t e = to_external ? launch_hist_transpose(in_slot, ext_f, 1, in.d.g, true, c->stream)
-                               : launch_hist_transpose(ext_f, in_slot, 1, in.d.g, false, c->stream);
-    if (e != hipSuccess) return c->hip(e, "history transpose");
-  }
-  return PIC_OK;
+  HistExport h{};
+  h.n = (int)slots.size();
+  std::copy(slots.begin(), slots.end(), h.s);
+  return c->hip(launch_hist_transpose(in.d.H, (double2*)ext, h, in.d.g, to_external, c->stream), "history transpose");
 }
 
 // one loop iteration of a multi-step call: field solve, then the gather/push
@@ -1338,7 +1326,7 @@ pic_status_t init_particles(pic_ctx_t c, int64_t n, const double* x, const doubl
     // inside a tile decay, enough to cost more in the fused pass than they
     // save in sorts).  A particle that outruns it takes
     // the global path until the next sort, so results never depend on it.
-    uint32_t* d_vmax = reinterpret_cast<uint32_t*>(c->d_diag);
+    uint32_t* d_vmax = c->d_vmax;
     uint32_t h_vmax = 0;
     st = c->hip(hipMemsetAsync(d_vmax, 0, sizeof(uint32_t), c->stream), "speed reset");
     if (!st) st = c->hip(launch_max_inplane(c->dtype, &pa, n, d_vmax, c->stream), "speed launch");
@@ -1470,24 +1458,23 @@ pic_status_t pic_diagnostics(pic_ctx_t c, double* out) {
   Instance& in = c->I();
   // the newest level is the one written by the last update: slots of s = nupd
   HistSlots hs = slots_of(c->hist, c->nupd);
-  pic_status_t st = c->hip(launch_field_diag(in.d.H, in.d.g, in.d.sc, hs, c->d_diag, c->stream), "field diag");
-  if (st) return st;
-  auto pa = parts_of(c, in.d, c->cur);
-  st = c->hip(launch_particle_diag(c->dtype, &pa, in.d.n, in.d.ph, c->d_diag + 16, c->stream), "particle diag");
-  if (st) return st;
-  std::vector<double> h(kDiagDoubles);
-  st = c->hip(hipMemcpyAsync(h.data(), c->d_diag, h.size() * 8, hipMemcpyDeviceToHost, c->stream), "diag copy");
-  if (st) return st;
-  st = c->hip(hipStreamSynchronize(c->stream), "diag sync");
-  if (st) return st;
-  for (int i = 0; i < 6; ++i) out[i] = h[i];
-  double ke = 0, bad = 0;
-  for (int b = 0; b < 256; ++b) {
-    ke += h[16 + 2 * b];
-    bad += h[16 + 2 * b + 1];
+  pic_status_t st = PIC_OK;
+  if (!c->h_diag) {
+    st = c->hip(hipHostMalloc(reinterpret_cast<void**>(&c->h_diag), kDiagDoubles * sizeof(double), hipHostMallocDefault),
+                "diagnostics buffer");
+    if (st) return st;
   }
-  out[6] = ke;
-  out[7] = bad;
+  auto pa = parts_of(c, in.d, c->cur);
+  st = c->hip(launch_diag(c->dtype, in.d.H, in.d.g, in.d.sc, hs, &pa, in.d.n, in.d.ph, c->h_diag, c->stream), "diagnostics");
+  if (!st) st = c->hip(hipStreamSynchronize(c->stream), "diag sync");
+  if (st) return st;
+  double v[10] = {0};
+  for (int b = 0; b < diag_field_blocks(in.d.g); ++b)
+    for (int k = 0; k < 8; ++k) v[k] += c->h_diag[kDiagField + 8 * b + k];
+  for (int b = 0; b < diag_part_blocks(in.d.n); ++b)
+    for (int k = 0; k < 2; ++k) v[8 + k] += c->h_diag[2 * b + k];
+  diag_values(v, in.d.g, out);
+  const double bad = out[7];
   return bad > 0 ? c->fail(PIC_ERR_NONFINITE, "non-finite particle values") : PIC_OK;
 }
 
@@ -1617,7 +1604,7 @@ static std::vector<std::array<size_t, 3>> state_segments(pic_ctx_t c, int cur, c
 // copy the segments between the state buffer and the context, in launches of
 // at most kCopyMax segments (one launch for a single-instance context)
 static pic_status_t copy_segments(pic_ctx_t c, const std::vector<std::array<size_t, 3>>& seg, char* state,
-                                  bool to_state) {
+                                  bool to_state, CopyHeader header = CopyHeader{}) {
   size_t k = 0;  // next segment to copy
   while (k < seg.size()) {
     CopyList L{};
@@ -1639,9 +1626,10 @@ static pic_status_t copy_segments(pic_ctx_t c, const std::vector<std::array<size
     if (!L.count) continue;
     L.first[L.count] = spans;
     if (spans > 0x7fffffffu) return c->fail(PIC_ERR_INVALID_ARG, "state copy larger than the grid allows");
-    hipLaunchKernelGGL(k_copy_list, dim3((unsigned)spans), dim3(kCopyThreads), 0, c->stream, L);
+    hipLaunchKernelGGL(k_copy_list, dim3((unsigned)spans), dim3(kCopyThreads), 0, c->stream, L, header);
     pic_status_t st = c->hip(hipGetLastError(), "state copy");
     if (st) return st;
+    header.count = 0;
   }
   return PIC_OK;
 }
@@ -1663,14 +1651,21 @@ pic_status_t pic_save_state_h(pic_ctx_t c, void* dst, int64_t* header) {
   for (size_t k = 0; k < sizeof(g) / sizeof(g[0]); ++k) words[k] = g[k];
   for (int i = 0; i < ni; ++i) words[kStateHeaderWords + i] = ns[i];
   pic_status_t st = PIC_OK;
-  for (size_t w0 = 0; w0 < words.size() && !st; w0 += kStateHeaderWords) {
+  CopyHeader ch{};
+  if (ni == 1) {  // written by the copy itself
+    ch.dst = reinterpret_cast<int64_t*>(b);
+    std::copy(words.begin(), words.begin() + kStateHeaderWords, ch.hw.w);
+    ch.last = words[kStateHeaderWords];
+    ch.count = kStateHeaderWords + 1;
+  }
+  for (size_t w0 = 0; ni > 1 && w0 < words.size() && !st; w0 += kStateHeaderWords) {
     HeaderWords hw{};
     for (int k = 0; k < kStateHeaderWords && w0 + k < words.size(); ++k) hw.w[k] = words[w0 + k];
     const int cnt = (int)std::min<size_t>(kStateHeaderWords, words.size() - w0);
     hipLaunchKernelGGL(k_state_header, dim3(1), dim3(64), 0, c->stream, reinterpret_cast<int64_t*>(b) + w0, hw, cnt);
     st = c->hip(hipGetLastError(), "state header");
   }
-  if (!st) st = copy_segments(c, state_segments(c, c->cur, ns, solved), b, true);
+  if (!st) st = copy_segments(c, state_segments(c, c->cur, ns, solved), b, true, ch);
   if (!st && header) std::memcpy(header, words.data(), words.size() * sizeof(int64_t));
   return st;
 }
@@ -1740,14 +1735,12 @@ pic_status_t pic_diagnostics_all(pic_ctx_t c, double* out) {
   for (int i = 0; i < n; ++i) {
     const InstDesc& d = c->inst[i].d;
     double* p = c->d_scratch + (size_t)i * kDiagDoubles;
-    pic_status_t st = c->hip(launch_field_diag(d.H, d.g, d.sc, hs, p, c->stream), "field diag");
-    if (st) return st;
     auto pa = parts_of(c, d, c->cur);
-    st = c->hip(launch_particle_diag(c->dtype, &pa, d.n, d.ph, p + 16, c->stream), "particle diag");
+    pic_status_t st =
+        c->hip(launch_diag(c->dtype, d.H, d.g, d.sc, hs, &pa, d.n, d.ph, p, c->stream), "diagnostics");
     if (st) return st;
   }
-  hipLaunchKernelGGL(k_diag_finalize, dim3(n), dim3(64), 0, c->stream, c->d_scratch, n, out);
-  return c->hip(hipGetLastError(), "diag finalize");
+  return c->hip(launch_diag_finalize(c->d_desc, n, c->d_scratch, out, c->stream), "diag finalize");
 }
 
 // ---------------------------------------------------------------------------

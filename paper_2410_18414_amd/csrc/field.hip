@@ -481,35 +481,76 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
   }
 }
 
-// history slot [nxh][ny] (internal) <-> [ny][nxh] (external)
-__global__ void k_hist_transpose(const double2* __restrict__ src, double2* __restrict__ dst, int nfield,
-                                 GridP g, int to_external) {
+// history slots [nxh][ny] (internal) <-> [ny][nxh] (external), every field of
+// the export in one launch: field f is slot slots.s[f], each block one 32 x 32
+// tile through LDS (both sides are read and written along their rows)
+__global__ void __launch_bounds__(256) k_hist_transpose(double2* __restrict__ H, double2* __restrict__ ext,
+                                                        HistExport slots, GridP g, int to_external) {
+  __shared__ double2 tile[32][33];
   const size_t plane = (size_t)g.nxh * g.ny;
-  for (size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x; t < plane * nfield;
-       t += (size_t)gridDim.x * blockDim.x) {
-    const size_t f = t / plane, r = t - f * plane;
-    if (to_external) {  // r = ky*nxh + kx
-      const size_t ky = r / g.nxh, kx = r - ky * g.nxh;
-      dst[t] = src[f * plane + kx * g.ny + ky];
-    } else {  // r = kx*ny + ky
-      const size_t kx = r / g.ny, ky = r - kx * g.ny;
-      dst[t] = src[f * plane + ky * g.nxh + kx];
-    }
-  }
+  double2* in = H + (size_t)slots.s[blockIdx.z] * plane;
+  double2* out = ext + (size_t)blockIdx.z * plane;
+  // rows of the source: kx of the internal layout, ky of the external one
+  const int rows = to_external ? g.nxh : g.ny, cols = to_external ? g.ny : g.nxh;
+  const double2* src = to_external ? in : out;
+  double2* dst = to_external ? out : in;
+  const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  for (int r = ty; r < 32; r += 8)
+    if (r0 + r < rows && c0 + tx < cols) tile[r][tx] = src[(size_t)(r0 + r) * cols + c0 + tx];
+  __syncthreads();
+  for (int r = ty; r < 32; r += 8)
+    if (c0 + r < cols && r0 + tx < rows) dst[(size_t)(c0 + r) * rows + r0 + tx] = tile[tx][r];
 }
 
-// Diagnostics over the half spectrum (one block).  Sums of w |f|^2 with
-// w = 1 on the kx = 0 and kx = nx/2 columns and 2 elsewhere (Parseval for the
-// half spectrum of a real field).
-template <int SCHEME>
-__global__ void __launch_bounds__(1024) k_field_diag(const double2* __restrict__ H, GridP g, SchemeCoef sc,
-                                                     HistSlots hs, double* __restrict__ out) {
-  __shared__ double red[6][1024];
+// Sums of the diagnostics, each block its own partials (summed later in block
+// order).  Blocks [0, nfield): over the half spectrum, eight sums at
+// out[kDiagField + 8 block]: |gauge|^2 and its two terms, |Gauss|^2 and its two
+// terms, the energy, and rho^ of the mean mode, each |f|^2 with w = 1 on the
+// kx = 0 and kx = nx/2 columns and 2 elsewhere (Parseval for the half spectrum
+// of a real field).  The other blocks: over the particles, the kinetic energy
+// (gamma - 1) m c^2 from v^n and the count of particles with a non-finite value,
+// at out[2 block].  One launch for both: a watched run waits for it (64 x 64 and
+// 32768 particles: 13 and 6 us apart, one field block, two reductions).
+template <int NV>
+__device__ __forceinline__ void block_sums(double (&v)[NV], double* __restrict__ out) {
+  __shared__ double red[4][NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    for (int off = 32; off; off >>= 1) v[i] += __shfl_xor(v[i], off);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int i = 0; i < NV; ++i) red[threadIdx.x >> 6][i] = v[i];
+  __syncthreads();
+  if (threadIdx.x < NV) out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+template <typename T, int SCHEME>
+__global__ void __launch_bounds__(256) k_diag(const double2* __restrict__ H, GridP g, SchemeCoef sc, HistSlots hs,
+                                              int nfield, Parts<T> p, int64_t n, PhysP ph, double* __restrict__ out) {
+  if ((int)blockIdx.x >= nfield) {
+    const int b = blockIdx.x - nfield, nb = gridDim.x - nfield;
+    double v[2] = {0.0, 0.0};
+    const double c2 = ph.c * ph.c;
+    for (int64_t i = b * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)nb * 256) {
+      const T* src[11] = {p.x, p.y, p.P[0], p.P[1], p.P[2], p.v[0], p.v[1], p.v[2], p.w[0], p.w[1], p.w[2]};
+      bool fin = true;
+#pragma unroll
+      for (int k = 0; k < 11; ++k) fin = fin && isfinite((double)src[k][i]);
+      if (!fin) {
+        v[1] += 1;
+        continue;
+      }
+      const double vx = p.v[0][i], vy = p.v[1][i], vz = p.v[2][i];
+      const double b2 = (vx * vx + vy * vy + vz * vz) / c2;
+      v[0] += (1.0 / sqrt(1.0 - b2) - 1.0) * ph.m * c2;
+    }
+    block_sums(v, out + 2 * b);
+    return;
+  }
   const size_t plane = (size_t)g.nxh * g.ny;
-  double acc[6] = {0, 0, 0, 0, 0, 0};  // gauge, gauge_t, gauge_d, gauss, rho+divE parts, energy
-  double accr = 0, accd = 0;
+  double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // gauge and its terms, Gauss and its terms, energy, mean rho^
   auto at = [&](int slot, size_t m) { return H[(size_t)slot * plane + m]; };
-  for (size_t m = threadIdx.x; m < plane; m += blockDim.x) {
+  for (size_t m = (size_t)blockIdx.x * 256 + threadIdx.x; m < plane; m += (size_t)nfield * 256) {
     const int kx = (int)(m / g.ny), ky = (int)(m - (size_t)kx * g.ny);
     const double kxs = kx_sym(kx, g), kys = ky_sym(ky, g);
     const double wgt = (kx == 0 || 2 * kx == g.nx) ? 1.0 : 2.0;
@@ -579,43 +620,32 @@ __global__ void __launch_bounds__(1024) k_field_diag(const double2* __restrict__
     acc[1] += wgt * n2(gt);
     acc[2] += wgt * n2(gd);
     acc[3] += wgt * n2(gauss);
-    accr += wgt * n2(rr);
-    accd += wgt * n2(divE);
-    acc[5] += wgt * (sc.eps0 * (n2(E[0]) + n2(E[1]) + n2(E[2])) + (n2(Bx) + n2(By) + n2(Bz)) / sc.mu0);
-    if (m == 0) acc[4] = rho.x;
+    acc[4] += wgt * n2(rr);
+    acc[5] += wgt * n2(divE);
+    acc[6] += wgt * (sc.eps0 * (n2(E[0]) + n2(E[1]) + n2(E[2])) + (n2(Bx) + n2(By) + n2(Bz)) / sc.mu0);
+    if (m == 0) acc[7] = rho.x;
   }
-  // rho and divE norms share slot 4's neighbours: pack them into the reduction
-  double vals[6] = {acc[0], acc[1], acc[2], acc[3], accr, accd};
-  double e = acc[5], ch = acc[4];
-  for (int i = 0; i < 6; ++i) red[i][threadIdx.x] = vals[i];
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
-      for (int i = 0; i < 6; ++i) red[i][threadIdx.x] += red[i][threadIdx.x + s];
-    __syncthreads();
+  block_sums(acc, out + kDiagField + 8 * blockIdx.x);
+}
+
+// pic_diagnostics' eight values of every instance from its block partials (one
+// wave per instance)
+__global__ void __launch_bounds__(64) k_diag_finalize(const InstDesc* __restrict__ D, const double* __restrict__ part,
+                                                      double* __restrict__ out) {
+  const InstDesc& d = D[blockIdx.x];
+  const double* p = part + (size_t)blockIdx.x * kDiagDoubles;
+  double v[10];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = (int)threadIdx.x < diag_field_blocks(d.g) ? p[kDiagField + 8 * threadIdx.x + k] : 0.0;
+  v[8] = v[9] = 0.0;
+  for (int b = threadIdx.x; b < diag_part_blocks(d.n); b += 64) {
+    v[8] += p[2 * b];
+    v[9] += p[2 * b + 1];
   }
-  double sums[6];
-  for (int i = 0; i < 6; ++i) sums[i] = red[i][0];
-  __syncthreads();
-  red[0][threadIdx.x] = e;
-  red[1][threadIdx.x] = ch;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + s];
-      red[1][threadIdx.x] += red[1][threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    const double norm = g.dx * g.dy / ((double)g.nx * g.ny);  // dx dy * (1/N) sum |f^|^2
-    out[0] = sqrt(norm * sums[0]);
-    out[1] = sqrt(norm * sums[1]) + sqrt(norm * sums[2]);
-    out[2] = sqrt(norm * sums[3]);
-    out[3] = sqrt(norm * sums[4]) + sqrt(norm * sums[5]);
-    out[4] = red[1][0] * g.dx * g.dy;
-    out[5] = 0.5 * norm * red[0][0];
-  }
+#pragma unroll
+  for (int k = 0; k < 10; ++k)
+    for (int off = 32; off; off >>= 1) v[k] += __shfl_xor(v[k], off);
+  if (threadIdx.x == 0) diag_values(v, d.g, out + blockIdx.x * PIC_DIAG_COUNT);
 }
 
 }  // namespace
@@ -738,23 +768,33 @@ hipError_t launch_rows_c2r(const InstDesc* D, int ninst, int nblocks, size_t lds
   return hipGetLastError();
 }
 
-hipError_t launch_hist_transpose(const double2* src, double2* dst, int nfield, GridP g, bool to_external,
+hipError_t launch_hist_transpose(double2* H, double2* ext, const HistExport& slots, GridP g, bool to_external,
                                  hipStream_t s) {
-  const size_t n = (size_t)g.nxh * g.ny * nfield;
-  const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_hist_transpose, dim3(blocks), dim3(256), 0, s, src, dst, nfield, g,
-                     to_external ? 1 : 0);
+  const int rows = to_external ? g.nxh : g.ny, cols = to_external ? g.ny : g.nxh;
+  hipLaunchKernelGGL(k_hist_transpose, dim3((cols + 31) / 32, (rows + 31) / 32, slots.n), dim3(256), 0, s, H, ext,
+                     slots, g, to_external ? 1 : 0);
   return hipGetLastError();
 }
 
-hipError_t launch_field_diag(const double2* H, GridP g, SchemeCoef sc, HistSlots hs, double* out,
-                             hipStream_t s) {
-  if (sc.scheme == PIC_SCHEME_BDF)
-    hipLaunchKernelGGL(k_field_diag<PIC_SCHEME_BDF>, dim3(1), dim3(1024), 0, s, H, g, sc, hs, out);
-  else if (sc.scheme == PIC_SCHEME_CDF2)
-    hipLaunchKernelGGL(k_field_diag<PIC_SCHEME_CDF2>, dim3(1), dim3(1024), 0, s, H, g, sc, hs, out);
-  else
-    hipLaunchKernelGGL(k_field_diag<PIC_SCHEME_DIRK2>, dim3(1), dim3(1024), 0, s, H, g, sc, hs, out);
+template <typename T>
+static hipError_t launch_diag_t(const double2* H, GridP g, const SchemeCoef& sc, const HistSlots& hs, const Parts<T>& p,
+                                int64_t n, PhysP ph, double* out, hipStream_t s) {
+  const int nf = diag_field_blocks(g);
+  const dim3 grid(nf + diag_part_blocks(n));
+  auto* fn = sc.scheme == PIC_SCHEME_BDF ? k_diag<T, PIC_SCHEME_BDF>
+             : sc.scheme == PIC_SCHEME_CDF2 ? k_diag<T, PIC_SCHEME_CDF2> : k_diag<T, PIC_SCHEME_DIRK2>;
+  hipLaunchKernelGGL(fn, grid, dim3(256), 0, s, H, g, sc, hs, nf, p, n, ph, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_diag(int dtype, const double2* H, GridP g, const SchemeCoef& sc, const HistSlots& hs,
+                       const void* parts, int64_t n, PhysP ph, double* out, hipStream_t s) {
+  return dtype == PIC_F32 ? launch_diag_t(H, g, sc, hs, *(const Parts<float>*)parts, n, ph, out, s)
+                          : launch_diag_t(H, g, sc, hs, *(const Parts<double>*)parts, n, ph, out, s);
+}
+
+hipError_t launch_diag_finalize(const InstDesc* D, int ninst, const double* part, double* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_diag_finalize, dim3(ninst), dim3(64), 0, s, D, part, out);
   return hipGetLastError();
 }
 

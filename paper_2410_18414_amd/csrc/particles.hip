@@ -154,42 +154,6 @@ __global__ void k_set_particles(Parts<T> p, int64_t n, const double* __restrict_
   p.id[i] = (int32_t)i;
 }
 
-// kinetic energy sum (gamma - 1) m c^2 from v^n, and a count of non-finite
-// values; per-block partials in out2[2*block + {0,1}]
-template <typename T>
-__global__ void __launch_bounds__(256) k_particle_diag(Parts<T> p, int64_t n, PhysP ph, double* out2) {
-  __shared__ double s0[256], s1[256];
-  double ke = 0, bad = 0;
-  const double c2 = ph.c * ph.c;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const T* src[11] = {p.x, p.y, p.P[0], p.P[1], p.P[2], p.v[0], p.v[1], p.v[2], p.w[0], p.w[1], p.w[2]};
-    bool fin = true;
-#pragma unroll
-    for (int k = 0; k < 11; ++k) fin = fin && isfinite((double)src[k][i]);
-    if (!fin) {
-      bad += 1;
-      continue;
-    }
-    const double vx = p.v[0][i], vy = p.v[1][i], vz = p.v[2][i];
-    const double b2 = (vx * vx + vy * vy + vz * vz) / c2;
-    ke += (1.0 / sqrt(1.0 - b2) - 1.0) * ph.m * c2;
-  }
-  s0[threadIdx.x] = ke;
-  s1[threadIdx.x] = bad;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      s0[threadIdx.x] += s0[threadIdx.x + s];
-      s1[threadIdx.x] += s1[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    out2[2 * blockIdx.x] = s0[0];
-    out2[2 * blockIdx.x + 1] = s1[0];
-  }
-}
-
 __global__ void k_fill_f64(double* p, size_t n, double v) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
     p[i] = v;
@@ -318,16 +282,6 @@ hipError_t launch_set_particles(int dtype, const void* parts, int64_t n, const d
   else
     hipLaunchKernelGGL(k_set_particles<double>, dim3(blocks_for(n)), dim3(256), 0, s, *(const Parts<double>*)parts, n,
                        in, g);
-  return hipGetLastError();
-}
-
-hipError_t launch_particle_diag(int dtype, const void* parts, int64_t n, PhysP ph, double* out2, hipStream_t s) {
-  if (dtype == PIC_F32)
-    hipLaunchKernelGGL(k_particle_diag<float>, dim3(256), dim3(256), 0, s, *(const Parts<float>*)parts, n, ph,
-                       out2);
-  else
-    hipLaunchKernelGGL(k_particle_diag<double>, dim3(256), dim3(256), 0, s, *(const Parts<double>*)parts, n, ph,
-                       out2);
   return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <string>
 
@@ -205,6 +206,12 @@ struct HistSlots {
   int vphi, vA, J[2], J_new;
 };
 
+// Slots of the exported history, in export order (BDF-6 has the most fields)
+struct HistExport {
+  int n;
+  int s[54];
+};
+
 // Tile decomposition for the sorted particle passes (tiles.hip)
 struct TileP {
   int nx, ny;      // mesh nodes
@@ -393,6 +400,31 @@ __device__ __forceinline__ int find_inst(const InstDesc* __restrict__ D, int nin
   return lo;
 }
 
+// Partial sums of the diagnostics of one instance: two per particle block, then
+// eight per field block (at most 256 and 64 blocks)
+constexpr int kDiagField = 512, kDiagDoubles = kDiagField + 8 * 64;
+__host__ __device__ inline int diag_field_blocks(const GridP& g) {
+  const int b = (g.nxh * g.ny + 511) / 512;
+  return b < 64 ? b : 64;
+}
+__host__ __device__ inline int diag_part_blocks(int64_t n) {
+  const int64_t b = (n + 255) / 256;
+  return (int)(b < 1 ? 1 : (b < 256 ? b : 256));
+}
+// pic_diagnostics' values from the sums over the blocks (eight field sums,
+// kinetic energy, non-finite count)
+__host__ __device__ inline void diag_values(const double* v, const GridP& g, double* out) {
+  const double norm = g.dx * g.dy / ((double)g.nx * g.ny);  // dx dy * (1/N) sum |f^|^2
+  out[0] = sqrt(norm * v[0]);
+  out[1] = sqrt(norm * v[1]) + sqrt(norm * v[2]);
+  out[2] = sqrt(norm * v[3]);
+  out[3] = sqrt(norm * v[4]) + sqrt(norm * v[5]);
+  out[4] = v[7] * g.dx * g.dy;
+  out[5] = 0.5 * norm * v[6];
+  out[6] = v[8];
+  out[7] = v[9];
+}
+
 // ---------------------------------------------------------------------------
 // launchers (each returns hipGetLastError() of its launches)
 
@@ -413,7 +445,6 @@ hipError_t launch_max_inplane(int dtype, const void* parts, int64_t n, uint32_t*
 // deterministic deposit: the int64 J planes of an instance as float64 (J export)
 hipError_t launch_j_export(const long long* src, double* dst, size_t n, double unscale, hipStream_t s);
 hipError_t launch_set_particles(int dtype, const void* parts, int64_t n, const double* in, GridP g, hipStream_t s);
-hipError_t launch_particle_diag(int dtype, const void* parts, int64_t n, PhysP ph, double* out2, hipStream_t s);
 
 // tiles.hip
 size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
@@ -454,7 +485,7 @@ hipError_t launch_columns(int scheme, int bdf_order, const InstDesc* D, int nins
 // f64out: the float64 mesh planes too (float32 contexts skip them in the step)
 hipError_t launch_rows_c2r(const InstDesc* D, int ninst, int nblocks, size_t lds, hipStream_t s, bool adj = false,
                            bool f64out = false);
-hipError_t launch_hist_transpose(const double2* src, double2* dst, int nfield, GridP g, bool to_external,
+hipError_t launch_hist_transpose(double2* H, double2* ext, const HistExport& slots, GridP g, bool to_external,
                                  hipStream_t s);
 // adjoint.hip (one float64 BDF-k instance; D[0])
 hipError_t launch_adj_push(int degree, const InstDesc* D, int64_t n, StepArgs sa, double* lam, int64_t ls,
@@ -476,6 +507,10 @@ hipError_t launch_adj_seed_energy(const double2* H, GridP g, SchemeCoef sc, Hist
                                   double* lam_hist, int nf, hipStream_t s);
 hipError_t launch_adj_initial(int64_t n, const double* P, PhysP ph, double* lam, hipStream_t s);
 
-hipError_t launch_field_diag(const double2* H, GridP g, SchemeCoef sc, HistSlots hs, double* out, hipStream_t s);
+// block partials of one instance's diagnostics (kDiagDoubles values), and the
+// eight values of every instance from them
+hipError_t launch_diag(int dtype, const double2* H, GridP g, const SchemeCoef& sc, const HistSlots& hs,
+                       const void* parts, int64_t n, PhysP ph, double* out, hipStream_t s);
+hipError_t launch_diag_finalize(const InstDesc* D, int ninst, const double* part, double* out, hipStream_t s);
 
 }  // namespace pic
