@@ -180,13 +180,13 @@ bool compatible(const pic_config_t& a, const pic_config_t& b, std::string& msg) 
 // Particles per chunk (workgroup) of the sorted passes, where the config leaves
 // them open: the candidate of least modelled time of the fused pass for
 // uniformly placed particles.  A tile's chunks have equal sizes.  A workgroup
-// costs its window load and flush, about 1.2 iterations of its 256 lanes, and
-// its iterations, a partly filled one nearly as much as a full one; the chip
-// holds `slots` workgroups (by LDS four float32 or two float64 ones per CU), and
+// costs its window load and flush, about 1.2 iterations of its 256 lanes (2.2 in
+// float64, whose windows are twice as large), and its iterations, in float32 a
+// partly filled one nearly as much as a full one; the chip holds `slots` workgroups (by LDS four float32 or two float64 ones per CU), and
 // about half a workgroup's time passes before the last ones end.  Measured
 // (fused pass, us, by particles per chunk): 128 x 128 with 1M float32 particles
-// 497: 33.0, 512 and a few: 35.6, 683: 32.2, 964: 33.2; float64 497: 70, 1024:
-// 64, 1365: 61, 2048: 60, 2731: 73; 256 x 256 with 2M float32 482: 46, 512 and a
+// 497: 33.0, 512 and a few: 35.6, 683: 32.2, 964: 33.2; float64 497: 70, 683:
+// 65, 1024: 64, 1365: 61, 2048: 60, 2731: 73; 256 x 256 with 2M float32 482: 46, 512 and a
 // few: 53, 683: 44.6, 910: 43.7; 64 x 64 with 32768 float64 256: 10.6, 512: 13.5.
 // Float32 candidates stay below twice the power of two (512 .. 4096, the largest
 // that leaves 8192 chunks) that fixes the deposit's scale.  Sets of at most 8192
@@ -213,6 +213,7 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
                               {rx ? (double)fy : 0.0, per_cell * rx * t.ts},
                               {ry ? (double)fx : 0.0, per_cell * ry * t.ts},
                               {rx && ry ? 1.0 : 0.0, per_cell * rx * ry}};
+  const double fixed = f32 ? 1.2 : 2.2;
   int best = base;
   double best_cost = 1e300;
   for (int chunk = 256; chunk < (f32 ? 2 * base : 8192); chunk += 16) {
@@ -223,14 +224,14 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
       items += k[0] * parts;
       const double size = k[1] / parts + std::sqrt(k[1]) / parts, whole = std::floor(size / 256.0);
       const double part = size / 256.0 - whole;
-      iters = std::max(iters, whole + (part > 0.0 ? std::max(0.7, part) : 0.0));
+      iters = std::max(iters, whole + (part > 0.0 && f32 ? std::max(0.7, part) : part));
     }
     // fewer workgroups than CUs: an iteration has the CU's units to itself
     const double load = n == total ? std::max(0.4, std::min(1.0, std::ceil(items / 256.0) / per_cu)) : 1.0;
     // rounds: workgroups start as others end, so a partial round costs more than
     // its share and less than a whole one
     const double share = items / slots, rounds = n == total ? 0.5 * (share + std::ceil(share)) : share;
-    const double cost = (std::max(1.0, rounds) + 0.5) * (1.2 + load * iters);
+    const double cost = (std::max(1.0, rounds) + 0.5) * (fixed + load * iters);
     if (cost < best_cost) {
       best_cost = cost;
       best = chunk;
@@ -1835,18 +1836,21 @@ pic_status_t step_adjoint(pic_ctx_t c, double* lam, double* lam_hist) {
   int max_lds = 0, dev = 0;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
-  const size_t lds_push = adj_tiled_lds_bytes(in.d.tp, true), lds_dep = adj_tiled_lds_bytes(in.d.tp, false);
+  // (the push adjoint's scatter by matrix instructions where its staging arrays
+  // fit beside the windows, by LDS atomics where only the windows do)
+  const bool mx = adj_tiled_lds_bytes(in.d.tp, true, true) <= (size_t)max_lds;
+  const size_t lds_push = adj_tiled_lds_bytes(in.d.tp, true, mx), lds_dep = adj_tiled_lds_bytes(in.d.tp, false, false);
   const bool tiled = c->sorted && lds_push <= (size_t)max_lds;
   const int geo = tiled_geometry(in.d.tp), nwb = c->nblk[BK_WORK];
   if (!st)
-    st = c->hip(tiled ? launch_adj_tiled(true, c->degree, geo, D, nwb, lds_push, sa, in.d.LAM, ls, c->stream)
+    st = c->hip(tiled ? launch_adj_tiled(true, c->degree, geo, D, nwb, lds_push, mx, sa, in.d.LAM, ls, c->stream)
                       : launch_adj_push(c->degree, D, in.d.n, sa, in.d.LAM, ls, c->stream),
                 "adjoint push");
   if (!st) st = c->hip(launch_rows_r2c(D, 1, 11 * (ny / in.d.R_r2c), c->lds_r2c, c->stream, true), "adjoint rows_r2c");
   if (!st) st = c->hip(launch_adj_columns(in.cfg.bdf_order, D, nx / 2 + 1, c->lds_adj_col, lam_hist, c->stream), "adjoint columns");
   if (!st) st = c->hip(launch_rows_c2r(D, 1, 2 * (ny / in.d.R_c2r), c->lds_c2r, c->stream, true), "adjoint rows_c2r");
   if (!st)
-    st = c->hip(tiled ? launch_adj_tiled(false, c->degree, geo, D, nwb, lds_dep, sa, in.d.LAM, ls, c->stream)
+    st = c->hip(tiled ? launch_adj_tiled(false, c->degree, geo, D, nwb, lds_dep, false, sa, in.d.LAM, ls, c->stream)
                       : launch_adj_deposit(c->degree, D, in.d.n, sa, in.d.LAM, ls, c->stream),
                 "adjoint deposit");
   if (!st && lam) st = pic_adjoint_get_particles(c, lam);

@@ -499,9 +499,9 @@ hipError_t launch_lam_follow(int64_t n, const int32_t* ids, double* LAM, double*
                              int32_t* LINV, int32_t* flag, hipStream_t s);
 // cell-sorted variants over the forward's chunks (push: mesh fields and their
 // adjoints in LDS windows; deposit: lambda_J window)
-size_t adj_tiled_lds_bytes(const TileP& tp, bool push);
-hipError_t launch_adj_tiled(bool push, int degree, int geo, const InstDesc* D, int nblocks, size_t lds, StepArgs sa,
-                            double* lam, int64_t ls, hipStream_t s);
+size_t adj_tiled_lds_bytes(const TileP& tp, bool push, bool mx);
+hipError_t launch_adj_tiled(bool push, int degree, int geo, const InstDesc* D, int nblocks, size_t lds, bool mx,
+                            StepArgs sa, double* lam, int64_t ls, hipStream_t s);
 hipError_t launch_adj_columns(int bdf_order, const InstDesc* D, int nxh, size_t lds, double* lam_hist, hipStream_t s);
 hipError_t launch_adj_seed_energy(const double2* H, GridP g, SchemeCoef sc, HistSlots hs, double scale,
                                   double* lam_hist, int nf, hipStream_t s);
