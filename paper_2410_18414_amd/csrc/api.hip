@@ -323,7 +323,7 @@ Layout plan_instance(const pic_config_t& c, int64_t total) {
   L.ccursor = take(ckeys * 4);
   L.twork = take((size_t)tp.max_work * 16);
   L.tnwork = take(4);
-  L.tdone = take(4);
+  L.tdone = take(8);  // and InstDesc::jread
   L.trank = take((size_t)cap * 4);
   L.tbucket = take((size_t)2 * kMaxBuckets * 4);
   if (c.flags & PIC_FLAG_ADJOINT) {
@@ -553,7 +553,7 @@ struct pic_ctx_s {
   double* h_diag = nullptr;  // pinned: pic_diagnostics' kernels write their partials to it (first call allocates)
   double* d_scratch = nullptr;  // scratch's address on the context's device
   int nblk[BK_NKINDS] = {0};
-  size_t lds_r2c = 0, lds_c2r = 0, lds_col = 0, lds_adj_col = 0, lds_tiled[3] = {0, 0, 0};
+  size_t lds_r2c = 0, lds_c2r = 0, lds_col = 0, lds_small = 0, lds_adj_col = 0, lds_tiled[3] = {0, 0, 0};
   int max_ny = 0;  // largest grid side in y over the instances (column kernel block size)
   int dtype = 0, degree = 3, scheme = 0;
   int split_items = 0;  // particles per thread of the bucket split (first sort)
@@ -745,12 +745,19 @@ pic_status_t particle_pass(pic_ctx_t c, int mode, bool may_sort = true) {
 pic_status_t do_solve(pic_ctx_t c) {
   auto* t = c->begin_timed(1);
   const int ni = c->ninst();
-  pic_status_t st = c->hip(launch_rows_r2c(c->d_desc, ni, c->nblk[BK_R2C], c->lds_r2c, c->stream), "rows_r2c");
-  if (!st)
-    st = c->hip(launch_columns(c->scheme, c->inst[0].cfg.bdf_order, c->d_desc, ni, c->nblk[BK_COL], c->lds_col,
-                               slots_of(c->hist, c->nupd), c->max_ny, c->stream),
-                "columns");
-  if (!st) st = c->hip(launch_rows_c2r(c->d_desc, ni, c->nblk[BK_C2R], c->lds_c2r, c->stream), "rows_c2r");
+  const HistSlots hs = slots_of(c->hist, c->nupd);
+  const int order = c->inst[0].cfg.bdf_order;
+  pic_status_t st = PIC_OK;
+  if (c->nblk[BK_SMALL])
+    st = c->hip(launch_solve_small(c->scheme, order, c->d_desc, ni, c->nblk[BK_SMALL], c->lds_small, hs, c->stream),
+                "solve");
+  if (c->nblk[BK_R2C]) {
+    if (!st) st = c->hip(launch_rows_r2c(c->d_desc, ni, c->nblk[BK_R2C], c->lds_r2c, c->stream), "rows_r2c");
+    if (!st)
+      st = c->hip(launch_columns(c->scheme, order, c->d_desc, ni, c->nblk[BK_COL], c->lds_col, hs, c->max_ny, c->stream),
+                  "columns");
+    if (!st) st = c->hip(launch_rows_c2r(c->d_desc, ni, c->nblk[BK_C2R], c->lds_c2r, c->stream), "rows_c2r");
+  }
   c->end_timed(t);
   if (st) return st;
   c->nupd += 1;
@@ -893,6 +900,12 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   int every = 64;
   std::vector<double> tw;
   hipError_t e = hipSuccess;
+  // the one-launch solve only where it is every instance's (two ways of solving
+  // follow one another: 64 uneven instances, five of them small, 2 % slower), and
+  // not with the deterministic flag, whose results are those of the instance
+  // alone, to the bit, in any ensemble
+  bool small = (cfgs[0].flags & PIC_FLAG_DETERMINISTIC) == 0;
+  for (int i = 0; i < ninst; ++i) small = small && solve_small(cfgs[i].nx, cfgs[i].ny, make_scheme(cfgs[i]));
   for (int i = 0; i < ninst && e == hipSuccess; ++i) {
     Instance& in = c->inst[i];
     const pic_config_t& cf = cfgs[i];
@@ -942,6 +955,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     d.tb.csize = (int32_t*)(b + in.L.tcsize);
     d.tb.nwork = (int32_t*)(b + in.L.tnwork);
     d.tb.done = (int32_t*)(b + in.L.tdone);
+    d.jread = d.tb.done + 1;
     d.tb.rank = (int32_t*)(b + in.L.trank);
     d.tb.bcount = (int32_t*)(b + in.L.tbucket);
     d.tb.bcursor = d.tb.bcount + kMaxBuckets;
@@ -989,12 +1003,13 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     d.R_c2r = rows_c2r_R(cf.nx, cf.ny);
     d.nb_col = columns_nb(cf.ny);
     // flattened block ranges
-    const int nb[BK_NKINDS] = {ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
-                               (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
-                               ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
+    const int nb[BK_NKINDS] = {small ? 0 : ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
+                               small ? 0 : (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
+                               small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
                                ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 1024),
                                ceil_div(d.tp.ntiles, 4),
-                               ceil_div(cf.max_particles, kSplitWidth * c->split_items)};
+                               ceil_div(cf.max_particles, kSplitWidth * c->split_items),
+                               small ? columns_parts(scheme_family(cf.scheme)) : 0};
     for (int k = 0; k < BK_NKINDS; ++k) {
       d.blk[k] = c->nblk[k];
       c->nblk[k] += nb[k];
@@ -1002,6 +1017,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     c->lds_r2c = std::max(c->lds_r2c, rows_r2c_lds_bytes(cf.nx, cf.ny));
     c->lds_c2r = std::max(c->lds_c2r, rows_c2r_lds_bytes(cf.nx, cf.ny));
     c->lds_col = std::max(c->lds_col, columns_split_lds_bytes(cf.ny, d.sc.substep ? d.sc.stages : 0));
+    if (small) c->lds_small = std::max(c->lds_small, solve_small_lds_bytes(cf.nx, cf.ny));
     c->max_ny = std::max(c->max_ny, cf.ny);
     if (cf.flags & PIC_FLAG_ADJOINT) c->lds_adj_col = std::max(c->lds_adj_col, adj_columns_lds_bytes(cf.ny));
     for (int mode = 0; mode < 3; ++mode)
@@ -1023,7 +1039,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     }
     if (e == hipSuccess) e = hipMemset(d.tb.count, 0, (size_t)d.tp.ntiles * 4);
     if (e == hipSuccess) e = hipMemset(d.tb.ccount, 0, (size_t)d.tp.ntiles * d.tp.ts * d.tp.ts * 4);
-    if (e == hipSuccess) e = hipMemset(d.tb.done, 0, 4);
+    if (e == hipSuccess) e = hipMemset(d.tb.done, 0, 8);
     if (e == hipSuccess) e = hipMemset(d.tb.bcount, 0, kMaxBuckets * 4);
   }
   c->sort_every = every;
@@ -1034,7 +1050,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     delete c;
     return PIC_ERR_HIP;
   }
-  size_t lds_need = std::max({c->lds_col, c->lds_adj_col, c->lds_r2c, c->lds_c2r});
+  size_t lds_need = std::max({c->lds_small, c->lds_col, c->lds_adj_col, c->lds_r2c, c->lds_c2r});
   if (c->sorted) lds_need = std::max({lds_need, c->lds_tiled[0], c->lds_tiled[1], c->lds_tiled[2]});
   if (lds_need > (size_t)max_lds) {
     g_err = "grid or tile too large for this device's LDS";
@@ -1425,9 +1441,10 @@ pic_status_t pic_get_field(pic_ctx_t c, int32_t which, double* dst) {
   }
   if (which == PIC_FIELD_MESH) {
     if (c->phase != SOLVED) return c->fail(PIC_ERR_STATE, "mesh fields are valid in phase SOLVED");
-    if (c->dtype == PIC_F32) {
+    if (c->dtype == PIC_F32 && c->nblk[BK_C2R]) {
       // the step writes only the float32 copy: the float64 planes from the
-      // solve's spectra (U is valid until the next solve)
+      // solve's spectra (U is valid until the next solve;
+      // the one-launch solve of a small grid writes both)
       pic_status_t st = c->hip(launch_rows_c2r(c->d_desc, c->ninst(), c->nblk[BK_C2R], c->lds_c2r, c->stream,
                                                false, true),
                                "mesh field export");

@@ -70,15 +70,16 @@ __device__ __forceinline__ void dft(double2 (&v)[R]) {
 // arithmetic and its two LDS round trips.  N = 128, two transforms: 1.04 us;
 // 1.24 us with run-time strides, 1.84 us with run-time divisions.  Radix 8 takes
 // fewer passes but gives the few busy waves three times the instructions: 1.7 us.
-template <bool INV>
+// Transforms are pitch apart (0: 2^lN).  LOOP: any number of butterflies.
+template <bool INV, bool LOOP>
 __device__ __forceinline__ double2* fft_pow2(double2* a, double2* b, const int lN, int B,
-                                             const double2* __restrict__ tw) {
-  const int lq = lN - 2, q = 1 << lq, t = threadIdx.x;
-  const bool act = t < B << lq;
-  const int j = t & (q - 1), fo = (t >> lq) << lN;
+                                             const double2* __restrict__ tw, int pitch) {
+  const int lq = lN - 2, q = 1 << lq, nt = B << lq, step = LOOP ? blockDim.x : 1 << 30;
+  auto row = [&](int t) { return pitch ? (t >> lq) * pitch : (t >> lq) << lN; };
 #pragma unroll
   for (int ls = 0; ls + 2 <= lN; ls += 2) {
-    if (act) {
+    for (int t = threadIdx.x; t < nt; t += step) {
+      const int j = t & (q - 1), fo = row(t);
       const double2* x = a + fo + j;
       double2 v[4] = {x[0], x[q], x[2 * q], x[3 * q]};
       const int k = j & ((1 << ls) - 1);
@@ -101,7 +102,8 @@ __device__ __forceinline__ double2* fft_pow2(double2* a, double2* b, const int l
   }
   if (lN & 1) {  // two butterflies per thread
     const int h = 2 * q;
-    if (act) {
+    for (int t = threadIdx.x; t < nt; t += step) {
+      const int j = t & (q - 1), fo = row(t);
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const double2 w = tw[j + u * q];
@@ -122,17 +124,18 @@ __device__ __forceinline__ double2* fft_pow2(double2* a, double2* b, const int l
 // have been combined.  Every value is wave-uniform.
 struct FftPass {
   int N, r, ns, q, stride;  // q = N / r butterflies, twiddle stride N / (r ns)
+  int pitch;                // from one transform to the next
   float inv_q, inv_ns;      // 1 / q, 1 / ns
 };
 
 template <int R, bool INV>
 __device__ __forceinline__ void fft_pass(const double2* a, double2* b, const FftPass& s, int B,
                                          const double2* __restrict__ tw) {
-  const int N = s.N, q = s.q, Ns = s.ns;
+  const int P = s.pitch, q = s.q, Ns = s.ns;
   for (int t = threadIdx.x; t < B * q; t += blockDim.x) {
     const int f = fdiv(t, s.inv_q), j = t - f * q;
     const int g = fdiv(j, s.inv_ns), k = j - g * Ns;
-    const double2* x = a + f * N + j;
+    const double2* x = a + f * P + j;
     double2 v[R], w[R];
 #pragma unroll
     for (int m = 0; m < R; ++m) v[m] = x[m * q];
@@ -144,7 +147,7 @@ __device__ __forceinline__ void fft_pass(const double2* a, double2* b, const Fft
       for (int m = 1; m < R; ++m) v[m] = cmul(v[m], INV ? cconj(w[m]) : w[m]);
     }
     dft<R, INV>(v);
-    double2* y = b + f * N + g * Ns * R + k;
+    double2* y = b + f * P + g * Ns * R + k;
 #pragma unroll
     for (int m = 0; m < R; ++m) y[m * Ns] = v[m];
   }
@@ -157,14 +160,14 @@ __device__ __forceinline__ void fft_pass(const double2* a, double2* b, const Fft
 template <bool INV>
 __device__ __forceinline__ void fft_pass_odd(double2* a, double2* b, const FftPass& s, int B,
                                              const double2* __restrict__ tw) {
-  const int N = s.N, q = s.q, Ns = s.ns, r = s.r, h = (r - 1) >> 1;
+  const int P = s.pitch, q = s.q, Ns = s.ns, r = s.r, h = (r - 1) >> 1;
   const float inv_h = __builtin_amdgcn_rcpf((float)h);
   for (int t = threadIdx.x; t < B * q * h; t += blockDim.x) {
     const int u = fdiv(t, inv_h);  // f * q + j
     const int m = t - u * h + 1;
     const int f = fdiv(u, s.inv_q), j = u - f * q;
     const int k = j - fdiv(j, s.inv_ns) * Ns;
-    double2* x = a + f * N + j;
+    double2* x = a + f * P + j;
     double2 v0 = x[m * q], v1 = x[(r - m) * q];
     if (Ns > 1) {
       const double2 w0 = tw[m * k * s.stride], w1 = tw[(r - m) * k * s.stride];
@@ -185,7 +188,7 @@ __device__ __forceinline__ void fft_pass_odd(double2* a, double2* b, const FftPa
     const int o = t - u * ho;
     const int f = fdiv(u, s.inv_q), j = u - f * q;
     const int g = fdiv(j, s.inv_ns), k = j - g * Ns;
-    const double2* x = a + f * N + j;
+    const double2* x = a + f * P + j;
     double2 ye[2], yo[2];
     ye[0] = ye[1] = x[0];
     yo[0] = yo[1] = make_double2(0.0, 0.0);
@@ -208,7 +211,7 @@ __device__ __forceinline__ void fft_pass_odd(double2* a, double2* b, const FftPa
         yo[c].y = __builtin_fma(df.y, -w.y, yo[c].y);
       }
     }
-    double2* y = b + f * N + g * Ns * r + k;
+    double2* y = b + f * P + g * Ns * r + k;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int oc = o + c * ho;
@@ -219,30 +222,39 @@ __device__ __forceinline__ void fft_pass_odd(double2* a, double2* b, const FftPa
   }
 }
 
-// B independent FFTs of the plan's length held in LDS at a[f*N + j] (Stockham
-// autosort: fft_pow2 for a power of two with one butterfly per thread, else the
-// passes of the plan's radices).  Ping-pongs between
-// a and b and returns the buffer holding the result.  tw[t] = exp(-2 pi i t / N),
+// B independent FFTs of the plan's length held in LDS at a[f*N + j] (f*pitch + j
+// if one is given; Stockham autosort: fft_pow2 for a power of two with one
+// butterfly per thread or up to 128 points, else the passes of the plan's
+// radices).  Ping-pongs between a and b and returns the buffer holding the result.  tw[t] = exp(-2 pi i t / N),
 // t < N.  INV: exp(+...) (unnormalised inverse).  All threads of the block must
 // call it; the caller synchronises before.
-template <bool INV>
+template <bool INV, bool LOOP = false>
 __device__ __forceinline__ double2* fft_lds(double2* a, double2* b, const FftPlan& p, int B,
-                                            const double2* __restrict__ tw) {
+                                            const double2* __restrict__ tw, int pitch = 0) {
   const int N = p.n;
-  if (B * N <= 4 * (int)blockDim.x) {
+  if constexpr (LOOP) {
     switch (N) {
-      case 8: return fft_pow2<INV>(a, b, 3, B, tw);
-      case 16: return fft_pow2<INV>(a, b, 4, B, tw);
-      case 32: return fft_pow2<INV>(a, b, 5, B, tw);
-      case 64: return fft_pow2<INV>(a, b, 6, B, tw);
-      case 128: return fft_pow2<INV>(a, b, 7, B, tw);
-      case 256: return fft_pow2<INV>(a, b, 8, B, tw);
-      case 512: return fft_pow2<INV>(a, b, 9, B, tw);
-      case 1024: return fft_pow2<INV>(a, b, 10, B, tw);
+      case 8: return fft_pow2<INV, true>(a, b, 3, B, tw, pitch);
+      case 16: return fft_pow2<INV, true>(a, b, 4, B, tw, pitch);
+      case 32: return fft_pow2<INV, true>(a, b, 5, B, tw, pitch);
+      case 64: return fft_pow2<INV, true>(a, b, 6, B, tw, pitch);
+      case 128: return fft_pow2<INV, true>(a, b, 7, B, tw, pitch);
+    }
+  } else if (B * N <= 4 * (int)blockDim.x) {
+    switch (N) {
+      case 8: return fft_pow2<INV, false>(a, b, 3, B, tw, pitch);
+      case 16: return fft_pow2<INV, false>(a, b, 4, B, tw, pitch);
+      case 32: return fft_pow2<INV, false>(a, b, 5, B, tw, pitch);
+      case 64: return fft_pow2<INV, false>(a, b, 6, B, tw, pitch);
+      case 128: return fft_pow2<INV, false>(a, b, 7, B, tw, pitch);
+      case 256: return fft_pow2<INV, false>(a, b, 8, B, tw, pitch);
+      case 512: return fft_pow2<INV, false>(a, b, 9, B, tw, pitch);
+      case 1024: return fft_pow2<INV, false>(a, b, 10, B, tw, pitch);
     }
   }
   FftPass s;
   s.N = N;
+  s.pitch = pitch ? pitch : N;
   s.ns = 1;
   uint64_t radices = p.radices[0], more = p.radices[1];
   while (s.ns < N) {

@@ -111,6 +111,225 @@ constexpr int kMaxStages = 3;  // DIRK stages: loops over them unrolled to this 
 // a bound of three waves per SIMD spills and is 5 us slower at 128 x 128)
 constexpr int kColMaxModes = 2;
 
+// The history terms of one mode's update that do not depend on J^{n+1} (BDF-k:
+// their sums); at(slot, mode) is that mode of a history slot.
+template <int SCHEME, int K, class At>
+__device__ __forceinline__ void load_terms(double2& o0, double2& o1, double2& o2, double2& o3, double2& o4, int ky, int part, int nst, bool naive_rho,
+                                           const HistSlots& hs, const SchemeCoef& sc, At at) {
+  const int c0 = part == 0 ? 0 : part - 1;
+  double2 h0, h1, h2, h3, h4;
+  h0 = h1 = h2 = h3 = h4 = make_double2(0.0, 0.0);
+  if (SCHEME == PIC_SCHEME_BDF) {
+    if (part == 0) {
+      // sum_j a_j rho^{n+1-j} (continuity only) and sum_i C_i phi^{n+1-i}
+      if (!naive_rho) {
+#pragma unroll
+        for (int j = 1; j <= K; ++j) h0 = cadd(h0, cscale(at(hs.rho[j - 1], ky), sc.a[j]));
+      }
+#pragma unroll
+      for (int i = 1; i <= 2 * K; ++i) h1 = cadd(h1, cscale(at(hs.phi[i - 1], ky), sc.Cn[i]));
+    } else {
+#pragma unroll
+      for (int i = 1; i <= 2 * K; ++i) h0 = cadd(h0, cscale(at(hs.A[i - 1] + c0, ky), sc.Cn[i]));
+    }
+  } else if (SCHEME == PIC_SCHEME_CDF2) {
+    if (part == 0) {
+      h0 = at(hs.rho[0], ky);
+      h1 = at(hs.rho[1], ky);
+      h2 = at(hs.phi[0], ky);
+      h3 = at(hs.phi[1], ky);
+    } else {
+      // J^{n-1} for the implicit form's averaged source, J^n for the others
+      h0 = at(hs.A[0] + c0, ky);
+      h1 = at(hs.A[1] + c0, ky);
+      h2 = at(hs.J[sc.form == 0 ? 1 : 0] + c0, ky);
+    }
+  } else {  // DIRK: u^n, v^n of the part's wave component, and J^n for interpolated stages
+    if (part == 0) {
+      h0 = at(hs.rho[0], ky);
+      h1 = at(hs.phi[0], ky);
+      h2 = at(hs.vphi, ky);
+      if (!nst && !naive_rho) {
+        h3 = at(hs.J[0], ky);
+        h4 = at(hs.J[0] + 1, ky);
+      }
+    } else {
+      h0 = at(hs.A[0] + c0, ky);
+      h1 = at(hs.vA + c0, ky);
+      if (!nst) h2 = at(hs.J[0] + c0, ky);
+    }
+  }
+  o0 = h0;
+  o1 = h1;
+  o2 = h2;
+  o3 = h3;
+  o4 = h4;
+}
+
+// The update of one mode of a part: writes its new history, returns what the
+// mesh fields are made of.  J(i): the mode's transformed currents.
+template <int SCHEME, int K, class At, class JAt>
+__device__ __forceinline__ double2 update_mode(double2 h0, double2 h1, double2 h2, double2 h3, double2 h4, int ky, double kxs, double kys, int part, int nst,
+                                               bool naive_rho, const HistSlots& hs, const SchemeCoef& sc, At at, JAt J) {
+  const int c0 = part == 0 ? 0 : part - 1;
+  const double Lh = 1.0 + (kxs * kxs + kys * kys) * sc.inv_alpha2;
+  double2 out;
+  // i k . V
+  auto divv = [&](double2 X, double2 Y) { return mul_i(make_double2(kxs * X.x + kys * Y.x, kxs * X.y + kys * Y.y)); };
+  if (SCHEME == PIC_SCHEME_DIRK2) {
+    // Sec. 3.3: s-stage DIRK on (u, v)' = (v, c^2 (S + Lap u)), Lap = -kappa,
+    // one scalar wave component per part
+    const double dt = sc.dt, c2 = sc.c * sc.c, kappa = kxs * kxs + kys * kys;
+    const int ns = sc.stages;
+    auto advance = [&](double2& u, double2& v, const double2* S) {
+      double2 ku[kMaxStages], kv[kMaxStages];
+#pragma unroll
+      for (int i = 0; i < kMaxStages; ++i) {
+        if (i >= ns) break;
+        double2 U = u, V = v;
+#pragma unroll
+        for (int j = 0; j < i; ++j) {
+          U = cadd(U, cscale(ku[j], dt * sc.dirkA[i][j]));
+          V = cadd(V, cscale(kv[j], dt * sc.dirkA[i][j]));
+        }
+        const double hai = dt * sc.dirkA[i][i];
+        const double Li = 1.0 + hai * hai * c2 * kappa;
+        const double2 src = csub(S[i], cscale(U, kappa));  // S + Lap U
+        ku[i] = cdivr(cadd(V, cscale(src, hai * c2)), Li);
+        kv[i] = cdivr(csub(cscale(src, c2), cscale(V, hai * c2 * kappa)), Li);
+      }
+#pragma unroll
+      for (int i = 0; i < kMaxStages; ++i) {
+        if (i >= ns) break;
+        u = cadd(u, cscale(ku[i], dt * sc.dirkB[i]));
+        v = cadd(v, cscale(kv[i], dt * sc.dirkB[i]));
+      }
+    };
+    double2 S[kMaxStages];
+    if (part == 0) {
+      const double2 rho_n = h0;
+      double2 rho = rho_n, rst[kMaxStages];
+      if (nst) {
+        // sub-stepped currents: rho^(i) are the RK stage values of the
+        // continuity equation, rho^{n+1} its final stage
+        double2 dv[kMaxStages];
+#pragma unroll
+        for (int i = 0; i < kMaxStages; ++i) {
+          if (i >= ns) break;
+          dv[i] = divv(J(2 * i), J(2 * i + 1));
+          rho = csub(rho, cscale(dv[i], dt * sc.dirkB[i]));
+        }
+#pragma unroll
+        for (int i = 0; i < kMaxStages; ++i) {
+          if (i >= ns) break;
+          rst[i] = rho_n;
+#pragma unroll
+          for (int j = 0; j <= i; ++j) rst[i] = csub(rst[i], cscale(dv[j], dt * sc.dirkA[i][j]));
+        }
+      } else {
+        if (naive_rho) {
+          rho = J(0);  // naive comparison: the deposited rho^{n+1}
+        } else {
+          const double2 J0 = J(0), J1 = J(1);
+#pragma unroll
+          for (int i = 0; i < kMaxStages; ++i) {
+            if (i >= ns) break;
+            const double2 X = cadd(cscale(h3, 1.0 - sc.dirkC[i]), cscale(J0, sc.dirkC[i]));
+            const double2 Y = cadd(cscale(h4, 1.0 - sc.dirkC[i]), cscale(J1, sc.dirkC[i]));
+            rho = csub(rho, cscale(divv(X, Y), dt * sc.dirkB[i]));
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kMaxStages; ++i)
+          if (i < ns) rst[i] = cadd(cscale(rho_n, 1.0 - sc.dirkC[i]), cscale(rho, sc.dirkC[i]));
+      }
+#pragma unroll
+      for (int i = 0; i < kMaxStages; ++i)
+        if (i < ns) S[i] = cscale(rst[i], 1.0 / sc.eps0);
+      double2 u = h1, v = h2;
+      advance(u, v, S);
+      at(hs.rho_new, ky) = rho;
+      at(hs.phi_new, ky) = u;
+      at(hs.vphi, ky) = v;
+      out = u;
+    } else {
+      double2 keep = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int i = 0; i < kMaxStages; ++i) {
+        if (i >= ns) break;
+        // stage current: sub-stepped, or interpolated between J^n and J^{n+1}
+        const double2 Ji = nst ? J(i)
+                               : cadd(cscale(h2, 1.0 - sc.dirkC[i]), cscale(J(0), sc.dirkC[i]));
+        S[i] = cscale(Ji, sc.mu0);
+        keep = cadd(keep, cscale(Ji, sc.dirkB[i]));
+      }
+      // J history: sum_i b_i J^(i) when sub-stepped, else J^{n+1}
+      if (!nst) keep = J(0);
+      double2 u = h0, v = h1;
+      advance(u, v, S);
+      at(hs.A_new + c0, ky) = u;
+      at(hs.vA + c0, ky) = v;
+      at(hs.J_new + c0, ky) = keep;
+      out = u;
+    }
+  } else if (part == 0) {
+    const double2 J0 = J(0), J1 = naive_rho ? J0 : J(1);
+    const double2 divJ = divv(J0, J1);  // i k . J
+    if (SCHEME == PIC_SCHEME_BDF) {
+      // continuity: sum_j a_j rho^{n+1-j} + dt div J^{n+1} = 0 (naive: the deposited rho)
+      const double2 rho = naive_rho ? J0 : cscale(cadd(cscale(divJ, sc.dt), h0), -1.0 / sc.a[0]);
+      const double2 phi = cdivr(csub(cscale(rho, sc.inv_alpha2 / sc.eps0), h1), Lh);
+      at(hs.rho_new, ky) = rho;
+      at(hs.phi_new, ky) = phi;
+      out = phi;
+    } else {
+      // rho^{n+3/2} from the staggered continuity equation; h0..h3 =
+      // rho^{n+1/2}, rho^{n-1/2}, phi^{n+1/2}, phi^{n-1/2}
+      const double2 rho = csub(h0, cscale(divJ, sc.dt));
+      double2 phi;
+      if (sc.form == 0) {  // implicit: sources averaged over n+3/2 and n-1/2
+        const double2 rhs = cadd(cscale(h2, 2.0), cscale(cadd(rho, h1), sc.inv_alpha2 / sc.eps0));
+        phi = csub(cdivr(rhs, Lh), h3);
+      } else if (sc.form == 1) {  // semi-implicit: source rho^{n+1/2}
+        const double2 rhs = cadd(cscale(h2, 2.0), cscale(h0, 2.0 * sc.inv_alpha2 / sc.eps0));
+        phi = csub(cdivr(rhs, Lh), h3);
+      } else {  // explicit: 2 phi - phi_old + c^2 dt^2 (Lap phi + rho/eps0), c^2 dt^2 = 2/alpha^2
+        const double kap = kxs * kxs + kys * kys;
+        phi = cadd(csub(cscale(h2, 2.0), h3),
+                   cscale(csub(cscale(h0, 1.0 / sc.eps0), cscale(h2, kap)), 2.0 * sc.inv_alpha2));
+      }
+      at(hs.rho_new, ky) = rho;
+      at(hs.phi_new, ky) = phi;
+      out = cscale(cadd(phi, h2), 0.5);
+    }
+  } else {
+    const double2 Jl = J(0);
+    if (SCHEME == PIC_SCHEME_BDF) {
+      const double2 A = cdivr(csub(cscale(Jl, sc.mu0 * sc.inv_alpha2), h0), Lh);
+      at(hs.A_new + c0, ky) = A;
+      out = A;
+    } else {
+      // h0, h1, h2 = A^n, A^{n-1}, and J^{n-1} (implicit) or J^n
+      double2 A;
+      if (sc.form == 0) {
+        const double2 r = cadd(cscale(h0, 2.0), cscale(cadd(Jl, h2), sc.mu0 * sc.inv_alpha2));
+        A = csub(cdivr(r, Lh), h1);
+      } else if (sc.form == 1) {
+        const double2 r = cadd(cscale(h0, 2.0), cscale(h2, 2.0 * sc.mu0 * sc.inv_alpha2));
+        A = csub(cdivr(r, Lh), h1);
+      } else {
+        const double kap = kxs * kxs + kys * kys;
+        A = cadd(csub(cscale(h0, 2.0), h1),
+                 cscale(csub(cscale(h2, sc.mu0), cscale(h0, kap)), 2.0 * sc.inv_alpha2));
+      }
+      at(hs.A_new + c0, ky) = A;
+      at(hs.J_new + c0, ky) = Jl;
+      out = A;
+    }
+  }
+  return out;
+}
+
 template <int SCHEME, int K>
 __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restrict__ D, int ninst, HistSlots hs) {
   // LDS: [0, N) the scaled output column; [N, 5N) work (two ping-pong pairs
@@ -157,48 +376,7 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
 #pragma unroll
   for (int m = 0; m < kColMaxModes; ++m) {
     const int ky = tid + m * nth;
-    h0[m] = h1[m] = h2[m] = h3[m] = h4[m] = make_double2(0.0, 0.0);
-    if (ky >= N) continue;
-    if (SCHEME == PIC_SCHEME_BDF) {
-      if (part == 0) {
-        // sum_j a_j rho^{n+1-j} (continuity only) and sum_i C_i phi^{n+1-i}
-        if (!naive_rho) {
-#pragma unroll
-          for (int j = 1; j <= K; ++j) h0[m] = cadd(h0[m], cscale(at(hs.rho[j - 1], ky), sc.a[j]));
-        }
-#pragma unroll
-        for (int i = 1; i <= 2 * K; ++i) h1[m] = cadd(h1[m], cscale(at(hs.phi[i - 1], ky), sc.Cn[i]));
-      } else {
-#pragma unroll
-        for (int i = 1; i <= 2 * K; ++i) h0[m] = cadd(h0[m], cscale(at(hs.A[i - 1] + c0, ky), sc.Cn[i]));
-      }
-    } else if (SCHEME == PIC_SCHEME_CDF2) {
-      if (part == 0) {
-        h0[m] = at(hs.rho[0], ky);
-        h1[m] = at(hs.rho[1], ky);
-        h2[m] = at(hs.phi[0], ky);
-        h3[m] = at(hs.phi[1], ky);
-      } else {
-        // J^{n-1} for the implicit form's averaged source, J^n for the others
-        h0[m] = at(hs.A[0] + c0, ky);
-        h1[m] = at(hs.A[1] + c0, ky);
-        h2[m] = at(hs.J[sc.form == 0 ? 1 : 0] + c0, ky);
-      }
-    } else {  // DIRK: u^n, v^n of the part's wave component, and J^n for interpolated stages
-      if (part == 0) {
-        h0[m] = at(hs.rho[0], ky);
-        h1[m] = at(hs.phi[0], ky);
-        h2[m] = at(hs.vphi, ky);
-        if (!nst && !naive_rho) {
-          h3[m] = at(hs.J[0], ky);
-          h4[m] = at(hs.J[0] + 1, ky);
-        }
-      } else {
-        h0[m] = at(hs.A[0] + c0, ky);
-        h1[m] = at(hs.vA + c0, ky);
-        if (!nst) h2[m] = at(hs.J[0] + c0, ky);
-      }
-    }
+    if (ky < N) load_terms<SCHEME, K>(h0[m], h1[m], h2[m], h3[m], h4[m], ky, part, nst, naive_rho, hs, sc, at);
   }
   __syncthreads();
   const double2* Jh;
@@ -227,161 +405,8 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
     const int ky = tid + m * nth;
     if (ky >= N) continue;
     const double kys = ky_sym(ky, g);
-    const double Lh = 1.0 + (kxs * kxs + kys * kys) * sc.inv_alpha2;
-    double2 out;
-    // i k . V
-    auto divv = [&](double2 X, double2 Y) { return mul_i(make_double2(kxs * X.x + kys * Y.x, kxs * X.y + kys * Y.y)); };
-    if (SCHEME == PIC_SCHEME_DIRK2) {
-      // Sec. 3.3: s-stage DIRK on (u, v)' = (v, c^2 (S + Lap u)), Lap = -kappa,
-      // one scalar wave component per part
-      const double h = sc.dt, c2 = sc.c * sc.c, kappa = kxs * kxs + kys * kys;
-      const int ns = sc.stages;
-      auto advance = [&](double2& u, double2& v, const double2* S) {
-        double2 ku[kMaxStages], kv[kMaxStages];
-#pragma unroll
-        for (int i = 0; i < kMaxStages; ++i) {
-          if (i >= ns) break;
-          double2 U = u, V = v;
-#pragma unroll
-          for (int j = 0; j < i; ++j) {
-            U = cadd(U, cscale(ku[j], h * sc.dirkA[i][j]));
-            V = cadd(V, cscale(kv[j], h * sc.dirkA[i][j]));
-          }
-          const double hai = h * sc.dirkA[i][i];
-          const double Li = 1.0 + hai * hai * c2 * kappa;
-          const double2 src = csub(S[i], cscale(U, kappa));  // S + Lap U
-          ku[i] = cdivr(cadd(V, cscale(src, hai * c2)), Li);
-          kv[i] = cdivr(csub(cscale(src, c2), cscale(V, hai * c2 * kappa)), Li);
-        }
-#pragma unroll
-        for (int i = 0; i < kMaxStages; ++i) {
-          if (i >= ns) break;
-          u = cadd(u, cscale(ku[i], h * sc.dirkB[i]));
-          v = cadd(v, cscale(kv[i], h * sc.dirkB[i]));
-        }
-      };
-      double2 S[kMaxStages];
-      if (part == 0) {
-        const double2 rho_n = h0[m];
-        double2 rho = rho_n, rst[kMaxStages];
-        if (nst) {
-          // sub-stepped currents: rho^(i) are the RK stage values of the
-          // continuity equation, rho^{n+1} its final stage
-          double2 dv[kMaxStages];
-#pragma unroll
-          for (int i = 0; i < kMaxStages; ++i) {
-            if (i >= ns) break;
-            dv[i] = divv(Jh[(2 * i) * N + ky], Jh[(2 * i + 1) * N + ky]);
-            rho = csub(rho, cscale(dv[i], h * sc.dirkB[i]));
-          }
-#pragma unroll
-          for (int i = 0; i < kMaxStages; ++i) {
-            if (i >= ns) break;
-            rst[i] = rho_n;
-#pragma unroll
-            for (int j = 0; j <= i; ++j) rst[i] = csub(rst[i], cscale(dv[j], h * sc.dirkA[i][j]));
-          }
-        } else {
-          if (naive_rho) {
-            rho = Jh[ky];  // naive comparison: the deposited rho^{n+1}
-          } else {
-            const double2 J0 = Jh[ky], J1 = Jh[N + ky];
-#pragma unroll
-            for (int i = 0; i < kMaxStages; ++i) {
-              if (i >= ns) break;
-              const double2 X = cadd(cscale(h3[m], 1.0 - sc.dirkC[i]), cscale(J0, sc.dirkC[i]));
-              const double2 Y = cadd(cscale(h4[m], 1.0 - sc.dirkC[i]), cscale(J1, sc.dirkC[i]));
-              rho = csub(rho, cscale(divv(X, Y), h * sc.dirkB[i]));
-            }
-          }
-#pragma unroll
-          for (int i = 0; i < kMaxStages; ++i)
-            if (i < ns) rst[i] = cadd(cscale(rho_n, 1.0 - sc.dirkC[i]), cscale(rho, sc.dirkC[i]));
-        }
-#pragma unroll
-        for (int i = 0; i < kMaxStages; ++i)
-          if (i < ns) S[i] = cscale(rst[i], 1.0 / sc.eps0);
-        double2 u = h1[m], v = h2[m];
-        advance(u, v, S);
-        at(hs.rho_new, ky) = rho;
-        at(hs.phi_new, ky) = u;
-        at(hs.vphi, ky) = v;
-        out = u;
-      } else {
-        double2 keep = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int i = 0; i < kMaxStages; ++i) {
-          if (i >= ns) break;
-          // stage current: sub-stepped, or interpolated between J^n and J^{n+1}
-          const double2 Ji = nst ? Jh[i * N + ky]
-                                 : cadd(cscale(h2[m], 1.0 - sc.dirkC[i]), cscale(Jh[ky], sc.dirkC[i]));
-          S[i] = cscale(Ji, sc.mu0);
-          keep = cadd(keep, cscale(Ji, sc.dirkB[i]));
-        }
-        // J history: sum_i b_i J^(i) when sub-stepped, else J^{n+1}
-        if (!nst) keep = Jh[ky];
-        double2 u = h0[m], v = h1[m];
-        advance(u, v, S);
-        at(hs.A_new + c0, ky) = u;
-        at(hs.vA + c0, ky) = v;
-        at(hs.J_new + c0, ky) = keep;
-        out = u;
-      }
-    } else if (part == 0) {
-      const double2 J0 = Jh[ky], J1 = naive_rho ? J0 : Jh[N + ky];
-      const double2 divJ = divv(J0, J1);  // i k . J
-      if (SCHEME == PIC_SCHEME_BDF) {
-        // continuity: sum_j a_j rho^{n+1-j} + dt div J^{n+1} = 0 (naive: the deposited rho)
-        const double2 rho = naive_rho ? J0 : cscale(cadd(cscale(divJ, sc.dt), h0[m]), -1.0 / sc.a[0]);
-        const double2 phi = cdivr(csub(cscale(rho, sc.inv_alpha2 / sc.eps0), h1[m]), Lh);
-        at(hs.rho_new, ky) = rho;
-        at(hs.phi_new, ky) = phi;
-        out = phi;
-      } else {
-        // rho^{n+3/2} from the staggered continuity equation; h0..h3 =
-        // rho^{n+1/2}, rho^{n-1/2}, phi^{n+1/2}, phi^{n-1/2}
-        const double2 rho = csub(h0[m], cscale(divJ, sc.dt));
-        double2 phi;
-        if (sc.form == 0) {  // implicit: sources averaged over n+3/2 and n-1/2
-          const double2 rhs = cadd(cscale(h2[m], 2.0), cscale(cadd(rho, h1[m]), sc.inv_alpha2 / sc.eps0));
-          phi = csub(cdivr(rhs, Lh), h3[m]);
-        } else if (sc.form == 1) {  // semi-implicit: source rho^{n+1/2}
-          const double2 rhs = cadd(cscale(h2[m], 2.0), cscale(h0[m], 2.0 * sc.inv_alpha2 / sc.eps0));
-          phi = csub(cdivr(rhs, Lh), h3[m]);
-        } else {  // explicit: 2 phi - phi_old + c^2 dt^2 (Lap phi + rho/eps0), c^2 dt^2 = 2/alpha^2
-          const double kap = kxs * kxs + kys * kys;
-          phi = cadd(csub(cscale(h2[m], 2.0), h3[m]),
-                     cscale(csub(cscale(h0[m], 1.0 / sc.eps0), cscale(h2[m], kap)), 2.0 * sc.inv_alpha2));
-        }
-        at(hs.rho_new, ky) = rho;
-        at(hs.phi_new, ky) = phi;
-        out = cscale(cadd(phi, h2[m]), 0.5);
-      }
-    } else {
-      const double2 Jl = Jh[ky];
-      if (SCHEME == PIC_SCHEME_BDF) {
-        const double2 A = cdivr(csub(cscale(Jl, sc.mu0 * sc.inv_alpha2), h0[m]), Lh);
-        at(hs.A_new + c0, ky) = A;
-        out = A;
-      } else {
-        // h0, h1, h2 = A^n, A^{n-1}, and J^{n-1} (implicit) or J^n
-        double2 A;
-        if (sc.form == 0) {
-          const double2 r = cadd(cscale(h0[m], 2.0), cscale(cadd(Jl, h2[m]), sc.mu0 * sc.inv_alpha2));
-          A = csub(cdivr(r, Lh), h1[m]);
-        } else if (sc.form == 1) {
-          const double2 r = cadd(cscale(h0[m], 2.0), cscale(h2[m], 2.0 * sc.mu0 * sc.inv_alpha2));
-          A = csub(cdivr(r, Lh), h1[m]);
-        } else {
-          const double kap = kxs * kxs + kys * kys;
-          A = cadd(csub(cscale(h0[m], 2.0), h1[m]),
-                   cscale(csub(cscale(h2[m], sc.mu0), cscale(h0[m], kap)), 2.0 * sc.inv_alpha2));
-        }
-        at(hs.A_new + c0, ky) = A;
-        at(hs.J_new + c0, ky) = Jl;
-        out = A;
-      }
-    }
+    const double2 out = update_mode<SCHEME, K>(h0[m], h1[m], h2[m], h3[m], h4[m], ky, kxs, kys, part, nst, naive_rho, hs, sc, at,
+                                               [&](int i) { return Jh[i * N + ky]; });
     store[ky] = cscale(out, scale);
   }
   __syncthreads();
@@ -478,6 +503,149 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
       F32[o * kFieldSlots + s0] = (float)z.x;
       F32[o * kFieldSlots + s0 + 1] = (float)z.y;
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The whole solve of a small grid in one launch: one block per part of the
+// column kernel above, which needs nothing from the other parts.  Part 0 makes
+// d_x phi, d_y phi and phi~ from J_x and J_y (naive mode: the deposited rho),
+// part 1 + l makes A_l, d_x A_l and d_y A_l from J_l; spectra and columns stay
+// in LDS.  Bound by a serial chain of twelve transform passes and five
+// transpositions on one CU (0.3 to 0.8 us each); the three kernels above add 2 us
+// of launch, load and store around each of three.  Solve, three launches and one:
+// 16 x 16 14.7 and 9.3 us, 32 x 32 15.2 and 13.4, 31 x 29 20.8 and 17.5; 64
+// instances of 32 x 32 51 and 18 us, 1024 of 16 x 16 313 and 140.  Up to
+// kSmallCells: at 40 x 40 18.4 and 20.5, at 64 x 64 15.8 and 33 us.
+// The last of the four blocks to have read J clears it for the next deposit
+// (InstDesc::jread counts them; nobody waits).
+constexpr int kSmallCells = 1024, kSmallThreads = 768;  // a mode per thread: at most 5 x 128
+
+// LDS: three buffers -- the spectra of a part's two outputs move between the
+// first two, then the rows of its three mesh fields between the free one and the
+// third -- and the twiddles of both axes: 75 KiB at 32 x 32, two blocks per CU
+__host__ __device__ inline int small_buffer(int nx, int ny) {
+  const int spec = 2 * (nx / 2 + 1) * (ny | 1), rows = 3 * ((ny + 1) / 2) * nx;
+  return spec > rows ? spec : rows;
+}
+
+template <int SCHEME, int K>
+__global__ void __launch_bounds__(kSmallThreads) k_solve_small(const InstDesc* __restrict__ D, int ninst, HistSlots hs) {
+  extern __shared__ double2 sm[];
+  __shared__ int last;
+  const int ii = find_inst(D, ninst, BK_SMALL, blockIdx.x);
+  const InstDesc& d = D[ii];
+  const GridP g = d.g;
+  const SchemeCoef& sc = d.sc;
+  const int part = blockIdx.x - d.blk[BK_SMALL];
+  const int nx = g.nx, ny = g.ny, nxh = g.nxh, cells = nx * ny, pitch = ny | 1, modes = nxh * ny;
+  const int tid = threadIdx.x, nth = kSmallThreads;
+  const int nbuf = small_buffer(nx, ny);
+  const bool naive_rho = part == 0 && d.naive;
+  const int ncol = part == 0 && !naive_rho ? 2 : 1;
+  const int c0 = part == 0 ? (naive_rho ? 3 : 0) : part - 1;
+  const float inv_ny = d.fy.inv_n, inv_nx = d.fx.inv_n, inv_nxh = __builtin_amdgcn_rcpf((float)nxh);
+  double2* X = sm;
+  double2* Y = sm + nbuf;
+  double2* Z = Y + nbuf;
+  double2* twx = Z + nbuf;
+  double2* twy = twx + nx;
+
+  // pairs of J's rows (of both planes, which follow one another)
+  const int rows = ncol * ny, nb = (rows + 1) >> 1;
+  {
+    const gptr<const double> J = gp((const double*)(d.J + (size_t)c0 * cells));
+    for (int t = tid; t < nb * nx; t += nth) {
+      const int b = fdiv(t, inv_nx), i = t + b * nx;  // row 2 b, column t - b nx
+      X[t] = make_double2(J[i], 2 * b + 1 < rows ? J[i + nx] : 0.0);
+    }
+  }
+  for (int i = tid; i < nx; i += nth) twx[i] = gc2(d.twx)[i];
+  for (int i = tid; i < ny; i += nth) twy[i] = gc2(d.twy)[i];
+  // history terms of this thread's mode
+  const GC2 H = gc2(d.H);
+  auto at = [&](int slot, int mode) -> decltype(auto) { return H[(size_t)slot * modes + mode]; };
+  double2 h0, h1, h2, h3, h4;
+  if (tid < modes) load_terms<SCHEME, K>(h0, h1, h2, h3, h4, tid, part, 0, naive_rho, hs, sc, at);
+  __syncthreads();
+  // this block's reads of J are in LDS
+  if (tid == 0) last = (__hip_atomic_fetch_add(d.jread, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 3) == 3;
+
+  const double2* z = fft_lds<false, true>(X, Y, d.fx, nb, twx);
+  double2* in = z == X ? Y : X;
+  // the two rows of each transform, into columns
+  for (int t = tid; t < nb * nxh; t += nth) {
+    const int b = fdiv(t, inv_nxh), k = t - b * nxh;
+    const double2 zk = z[b * nx + k], zn = cconj(z[b * nx + (k ? nx - k : 0)]);
+    const double2 dd = csub(zk, zn);
+    const int r0 = 2 * b, r1 = r0 + 1;
+    const int p0 = r0 >= ny ? 1 : 0, p1 = r1 >= ny ? 1 : 0;
+    in[(p0 * nxh + k) * pitch + r0 - p0 * ny] = cscale(cadd(zk, zn), 0.5);
+    if (r1 < rows) in[(p1 * nxh + k) * pitch + r1 - p1 * ny] = make_double2(0.5 * dd.y, -0.5 * dd.x);
+  }
+  __syncthreads();
+  const double2* Jh = fft_lds<false, true>(in, in == X ? Y : X, d.fy, ncol * nxh, twy, pitch);
+  double2* G = Jh == X ? Y : X;  // the outputs' spectra: the field and its y derivative
+  const double scale = 1.0 / ((double)nx * ny);
+  if (tid < modes) {
+    const int kx = fdiv(tid, inv_ny), ky = tid - kx * ny, o = kx * pitch + ky;
+    const double kys = ky_sym(ky, g);
+    const double2 out = cscale(update_mode<SCHEME, K>(h0, h1, h2, h3, h4, tid, kx_sym(kx, g), kys, part, 0, naive_rho,
+                                                      hs, sc, at, [&](int i) { return Jh[i * nxh * pitch + o]; }),
+                               scale);
+    G[o] = out;
+    G[nxh * pitch + o] = mul_i(cscale(out, kys));
+  }
+  __syncthreads();
+  const double2* U = fft_lds<true, true>(G, G == X ? Y : X, d.fy, 2 * nxh, twy, pitch);
+  // the three mesh fields, pairs of rows
+  double2* a = U == X ? Y : X;
+  const int hy = (ny + 1) >> 1;
+  const float inv_hy = __builtin_amdgcn_rcpf((float)hy);
+  const int nyq = (nx & 1) ? -1 : nx >> 1;
+  const gptr<double> F64 = gp(d.F64);
+  const gptr<float> F32 = gp(d.F32);
+  // the part's fields: the output, its x derivative, its y derivative
+  auto slot_of = [&](int f) { return part == 0 ? (f == 0 ? 11 : f - 1) : part + 1 + 3 * f; };
+  for (int t = tid; t < 3 * hy * nxh; t += nth) {
+    const int row = fdiv(t, inv_nxh), k = t - row * nxh;
+    const int f = fdiv(row, inv_hy), y = 2 * (row - f * hy);
+    const double2* u = U + ((f == 2 ? nxh : 0) + k) * pitch + y;
+    double2 P = u[0], Q = make_double2(0.0, 0.0);
+    if (y + 1 < ny) Q = u[1];
+    if (f == 1) {
+      const double kxs = 2.0 * M_PI * k / g.lx * ((k == nyq) ? 0.0 : 1.0);
+      P = mul_i(cscale(P, kxs));
+      Q = mul_i(cscale(Q, kxs));
+    }
+    if (k == 0 || k == nyq) {  // real-signal spectrum: these bins are real
+      P.y = 0.0;
+      Q.y = 0.0;
+    }
+    a[row * nx + k] = cadd(P, mul_i(Q));
+    if (k > 0 && k != nyq) a[row * nx + nx - k] = cadd(cconj(P), mul_i(cconj(Q)));
+  }
+  __syncthreads();
+  const double2* res = fft_lds<true, true>(a, Z, d.fx, 3 * hy, twx);
+  for (int t = tid; t < 3 * hy * nx; t += nth) {
+    const int row = fdiv(t, inv_nx), x = t - row * nx;
+    const int f = fdiv(row, inv_hy), y = 2 * (row - f * hy), s = slot_of(f);
+    const int o = y * nx + x;
+    const double2 v = res[t];
+    const bool two = y + 1 < ny;
+    // the float64 planes too where the particles are float32: they are what
+    // the mesh-field export copies
+    F64[(size_t)s * cells + o] = v.x;
+    if (two) F64[(size_t)s * cells + o + nx] = v.y;
+    if (F32) {
+      F32[(size_t)o * kFieldSlots + s] = (float)v.x;
+      if (two) F32[(size_t)(o + nx) * kFieldSlots + s] = (float)v.y;
+    }
+  }
+  if (last) {  // ready for the next deposit (naive: rho restarts from the ion background)
+    const gptr<double> J = gp(d.J);
+    const gptr<const double> RB = gp((const double*)d.RB);
+    for (int i = tid; i < j_planes(sc, d.naive) * cells; i += nth) J[i] = i < 3 * cells ? 0.0 : RB[i - 3 * cells];
   }
 }
 
@@ -747,6 +915,33 @@ hipError_t launch_columns(int scheme, int bdf_order, const InstDesc* D, int nins
     case 4: return launch_columns_split_t<PIC_SCHEME_BDF, 4>(D, ninst, nblocks, lds, hs, max_ny, s);
     case 5: return launch_columns_split_t<PIC_SCHEME_BDF, 5>(D, ninst, nblocks, lds, hs, max_ny, s);
     default: return launch_columns_split_t<PIC_SCHEME_BDF, 6>(D, ninst, nblocks, lds, hs, max_ny, s);
+  }
+}
+
+template <int SCHEME, int K>
+static hipError_t launch_solve_small_t(const InstDesc* D, int ninst, int nblocks, size_t lds, HistSlots hs,
+                                       hipStream_t s) {
+  (void)hipFuncSetAttribute((const void*)k_solve_small<SCHEME, K>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipLaunchKernelGGL((k_solve_small<SCHEME, K>), dim3(nblocks), dim3(kSmallThreads), lds, s, D, ninst, hs);
+  return hipGetLastError();
+}
+
+size_t solve_small_lds_bytes(int nx, int ny) { return (size_t)(3 * small_buffer(nx, ny) + nx + ny) * sizeof(double2); }
+bool solve_small(int nx, int ny, const SchemeCoef& sc) {
+  return !sc.substep && nx * ny <= kSmallCells && (nx / 2 + 1) * ny <= kSmallThreads;
+}
+
+hipError_t launch_solve_small(int scheme, int bdf_order, const InstDesc* D, int ninst, int nblocks, size_t lds,
+                              HistSlots hs, hipStream_t s) {
+  if (scheme == PIC_SCHEME_CDF2) return launch_solve_small_t<PIC_SCHEME_CDF2, 0>(D, ninst, nblocks, lds, hs, s);
+  if (scheme == PIC_SCHEME_DIRK2) return launch_solve_small_t<PIC_SCHEME_DIRK2, 0>(D, ninst, nblocks, lds, hs, s);
+  switch (bdf_order) {
+    case 1: return launch_solve_small_t<PIC_SCHEME_BDF, 1>(D, ninst, nblocks, lds, hs, s);
+    case 2: return launch_solve_small_t<PIC_SCHEME_BDF, 2>(D, ninst, nblocks, lds, hs, s);
+    case 3: return launch_solve_small_t<PIC_SCHEME_BDF, 3>(D, ninst, nblocks, lds, hs, s);
+    case 4: return launch_solve_small_t<PIC_SCHEME_BDF, 4>(D, ninst, nblocks, lds, hs, s);
+    case 5: return launch_solve_small_t<PIC_SCHEME_BDF, 5>(D, ninst, nblocks, lds, hs, s);
+    default: return launch_solve_small_t<PIC_SCHEME_BDF, 6>(D, ninst, nblocks, lds, hs, s);
   }
 }
 

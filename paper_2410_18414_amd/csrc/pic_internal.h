@@ -311,7 +311,7 @@ __device__ __forceinline__ int udiv_exact(int a, int b) {
 
 // block ranges of the flattened kernels
 enum BlockKind {
-  BK_R2C = 0,    // (ny/R_r2c) x 3 blocks
+  BK_R2C = 0,    // (ny/R_r2c) x 3 blocks (this and the next two: none where solve_small)
   BK_COL = 1,    // nxh x columns_parts(scheme) blocks
   BK_C2R = 2,    // (ny/R_c2r) x 6 blocks
   BK_WORK = 3,   // tp.max_work blocks (tiled particle pass)
@@ -319,7 +319,8 @@ enum BlockKind {
   BK_COUNT = 5,  // ceil(capacity/1024) blocks (tile counting)
   BK_TILES = 6,  // ceil(ntiles/4) blocks (per-tile cell scan, one wave per tile)
   BK_SPLIT = 7,  // ceil(capacity/(kSplitWidth split_items)) blocks (bucket split)
-  BK_NKINDS = 8
+  BK_SMALL = 8,  // 4 blocks where the whole solve is one launch (solve_small), else none
+  BK_NKINDS = 9
 };
 
 // One instance of the method: static for the life of a context.
@@ -355,6 +356,7 @@ struct InstDesc {
   int qe_det;               // that scale's exponent (float32: every chunk's window scale too)
   double det_scale, det_unscale;  // 2^qe_det, 2^-qe_det
   TileBufs tb;
+  int32_t* jread;           // blocks of the one-launch solve that have read J, over all solves
   int64_t n;                // particles loaded
   int R_r2c, R_c2r, nb_col; // rows per block of the row kernels; forward batch of the adjoint column kernel
   int blk[BK_NKINDS];       // first block of this instance in each flattened grid
@@ -485,6 +487,11 @@ hipError_t launch_columns(int scheme, int bdf_order, const InstDesc* D, int nins
 // f64out: the float64 mesh planes too (float32 contexts skip them in the step)
 hipError_t launch_rows_c2r(const InstDesc* D, int ninst, int nblocks, size_t lds, hipStream_t s, bool adj = false,
                            bool f64out = false);
+// the solve of a small grid in one launch (the rule, its LDS bytes, the launch)
+bool solve_small(int nx, int ny, const SchemeCoef& sc);
+size_t solve_small_lds_bytes(int nx, int ny);
+hipError_t launch_solve_small(int scheme, int bdf_order, const InstDesc* D, int ninst, int nblocks, size_t lds,
+                              HistSlots hs, hipStream_t s);
 hipError_t launch_hist_transpose(double2* H, double2* ext, const HistExport& slots, GridP g, bool to_external,
                                  hipStream_t s);
 // adjoint.hip (one float64 BDF-k instance; D[0])
