@@ -340,9 +340,10 @@ Layout plan_instance(const pic_config_t& c, int64_t total) {
   return L;
 }
 
-// context-level buffers ahead of the instances: descriptors, and the word the
-// loading's largest speed is found in
-size_t head_bytes(int ninst) { return align_up(ninst * sizeof(InstDesc)) + kAlign; }
+// context-level buffers ahead of the instances: descriptors and their first
+// blocks, and the word the loading's largest speed is found in
+size_t desc_bytes(size_t ninst) { return ninst * (sizeof(InstDesc) + BK_NKINDS * sizeof(int)); }
+size_t head_bytes(int ninst) { return align_up(desc_bytes(ninst)) + kAlign; }
 
 int64_t total_capacity(const pic_config_t* cfgs, int ninst) {
   int64_t n = 0;
@@ -666,9 +667,15 @@ struct pic_ctx_s {
   }
   // upload the host descriptors (synchronises the stream; not on the step path)
   pic_status_t upload_desc() {
-    std::vector<InstDesc> h(inst.size());
-    for (size_t i = 0; i < inst.size(); ++i) h[i] = inst[i].d;
-    hipError_t e = hipMemcpyAsync(d_desc, h.data(), h.size() * sizeof(InstDesc), hipMemcpyHostToDevice, stream);
+    const size_t n = inst.size();
+    std::vector<char> h(desc_bytes(n));
+    InstDesc* D = reinterpret_cast<InstDesc*>(h.data());
+    int* first = reinterpret_cast<int*>(D + n);  // [kind][instance], find_inst
+    for (size_t i = 0; i < n; ++i) {
+      D[i] = inst[i].d;
+      for (int k = 0; k < BK_NKINDS; ++k) first[k * n + i] = inst[i].d.blk[k];
+    }
+    hipError_t e = hipMemcpyAsync(d_desc, D, h.size(), hipMemcpyHostToDevice, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     return hip(e, "descriptor upload");
   }
@@ -892,7 +899,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   c->scheme = scheme_family(cfgs[0].scheme);
   c->sorted = (cfgs[0].flags & PIC_FLAG_NO_SORT) == 0;
   c->d_desc = (InstDesc*)c->ws;
-  c->d_vmax = (uint32_t*)(c->ws + align_up(ninst * sizeof(InstDesc)));
+  c->d_vmax = (uint32_t*)(c->ws + align_up(desc_bytes(ninst)));
   c->inst.resize(ninst);
   const int64_t cap = total_capacity(cfgs, ninst);
   c->split_items = split_items(cap, c->dtype == PIC_F32 ? 4 : 8);
