@@ -558,6 +558,7 @@ struct pic_ctx_s {
   int max_ny = 0;  // largest grid side in y over the instances (column kernel block size)
   int dtype = 0, degree = 3, scheme = 0;
   int split_items = 0;  // particles per thread of the bucket split (first sort)
+  int count_items = 0;  // particles per thread of the tile count
   int geo = 0;  // compiled window geometry shared by every instance (0: none, runtime geometry)
   bool sorted = true;
   int sort_every = 4;
@@ -688,6 +689,10 @@ namespace {
 // 60 us straight and 72 through buckets at 131072 particles, 82 and 79 at
 // 262144, 233 and 125 at 1M; export 41 and 55 us at 262144, 146 and 100 at 1M
 constexpr int64_t kFirstSortMin = 1 << 18, kExportMin = 1 << 19;
+// particles from which on a thread counts four for the sort, else one: float32
+// count pass 8.7 us with one and 9.9 with four at 1M, 19.7 and 16.3 at 2M, 503 and
+// 318 at 67M; float64, 32768 particles 6.5 and 12.9
+constexpr int64_t kCountWide = 3 << 19;
 
 // counting sort of every instance's particles by tile into the other set
 pic_status_t do_sort(pic_ctx_t c) {
@@ -701,7 +706,7 @@ pic_status_t do_sort(pic_ctx_t c) {
   const hipError_t e =
       first ? launch_first_sort(c->dtype, c->d_desc, c->ninst(), c->split_items, c->nblk[BK_SPLIT], c->nblk[BK_TILES],
                                 c->cur, c->stream)
-            : launch_tile_sort(c->dtype, c->d_desc, c->ninst(), c->nblk[BK_COUNT], c->nblk[BK_TILES],
+            : launch_tile_sort(c->dtype, c->d_desc, c->ninst(), c->count_items, c->nblk[BK_COUNT], c->nblk[BK_TILES],
                                c->nblk[BK_PART], c->cur, c->stream);
   c->end_timed(t);
   pic_status_t st = c->hip(e, "tile sort");
@@ -902,6 +907,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
   c->d_vmax = (uint32_t*)(c->ws + align_up(desc_bytes(ninst)));
   c->inst.resize(ninst);
   const int64_t cap = total_capacity(cfgs, ninst);
+  c->count_items = cap < kCountWide ? 1 : 4;
   c->split_items = split_items(cap, c->dtype == PIC_F32 ? 4 : 8);
   size_t off = head_bytes(ninst);
   int every = 64;
@@ -1013,7 +1019,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     const int nb[BK_NKINDS] = {small ? 0 : ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
                                small ? 0 : (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
                                small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
-                               ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 1024),
+                               ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 256 * c->count_items),
                                ceil_div(d.tp.ntiles, 4),
                                ceil_div(cf.max_particles, kSplitWidth * c->split_items),
                                small ? columns_parts(scheme_family(cf.scheme)) : 0};

@@ -316,7 +316,7 @@ enum BlockKind {
   BK_C2R = 2,    // (ny/R_c2r) x 6 blocks
   BK_WORK = 3,   // tp.max_work blocks (tiled particle pass)
   BK_PART = 4,   // ceil(capacity/256) blocks (untiled passes, scatter)
-  BK_COUNT = 5,  // ceil(capacity/1024) blocks (tile counting)
+  BK_COUNT = 5,  // ceil(capacity/(256 count_items)) blocks (tile counting)
   BK_TILES = 6,  // ceil(ntiles/4) blocks (per-tile cell scan, one wave per tile)
   BK_SPLIT = 7,  // ceil(capacity/(kSplitWidth split_items)) blocks (bucket split)
   BK_SMALL = 8,  // 4 blocks where the whole solve is one launch (solve_small), else none
@@ -459,7 +459,7 @@ hipError_t launch_set_particles(int dtype, const void* parts, int64_t n, const d
 
 // tiles.hip
 size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
-hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int nb_count, int nb_tiles, int nb_part,
+hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int count_items, int nb_count, int nb_tiles, int nb_part,
                             int src_set, hipStream_t s);
 hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s);
 // reorder.hip: the sort of sets in no known order (src -> src, by way of
