@@ -1012,8 +1012,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     }
     d.RB = d.naive ? (double*)(b + in.L.RB) : nullptr;
     d.n = 0;
-    d.R_r2c = rows_r2c_R(cf.nx, cf.ny);
-    d.R_c2r = rows_c2r_R(cf.nx, cf.ny);
+    d.R_r2c = rows_r2c_R(cf.nx, cf.ny, ninst);
+    d.R_c2r = rows_c2r_R(cf.nx, cf.ny, ninst);
     d.nb_col = columns_nb(cf.ny);
     // flattened block ranges
     const int nb[BK_NKINDS] = {small ? 0 : ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
@@ -1027,8 +1027,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
       d.blk[k] = c->nblk[k];
       c->nblk[k] += nb[k];
     }
-    c->lds_r2c = std::max(c->lds_r2c, rows_r2c_lds_bytes(cf.nx, cf.ny));
-    c->lds_c2r = std::max(c->lds_c2r, rows_c2r_lds_bytes(cf.nx, cf.ny));
+    c->lds_r2c = std::max(c->lds_r2c, rows_r2c_lds_bytes(cf.nx, d.R_r2c));
+    c->lds_c2r = std::max(c->lds_c2r, rows_c2r_lds_bytes(cf.nx, d.R_c2r));
     c->lds_col = std::max(c->lds_col, columns_split_lds_bytes(cf.ny, d.sc.substep ? d.sc.stages : 0));
     if (small) c->lds_small = std::max(c->lds_small, solve_small_lds_bytes(cf.nx, cf.ny));
     c->max_ny = std::max(c->max_ny, cf.ny);

@@ -853,25 +853,35 @@ FftPlan plan_fft(int n) {
 
 // rows per block of the row kernels: at most 8, within the LDS budget, and
 // small enough that one instance's transform has 256 blocks or more (the row
-// kernels are latency-bound: more, shorter blocks finish sooner).  C2R keeps
-// R nx <= 1024: its (2 R + 1) nx complex values of LDS then let three blocks
-// share a CU at nx = 512 (two rows per block there: the solve 4 us faster
-// than with four)
-int rows_r2c_R(int nx, int ny) {
+// kernels are latency-bound: more, shorter blocks finish sooner).  An ensemble
+// has its blocks from many instances: each needs only its part of 1024, and up to
+// 16 rows give a block of short rows enough butterflies for its waves (two rows
+// of 64 are 32 of them for 256 threads).  Solve of 64 uneven grids with one
+// instance's rule and this one: sides of powers of two 273 and 218 us, any sides
+// 497 and 448; with at most 8 rows 234 and 467.  C2R keeps R nx <= 1024: its
+// (2 R + 1) nx complex values of LDS then let three blocks share a CU at nx = 512
+// (two rows per block there: the solve 4 us faster than with four; 2048: the
+// ensembles' solve 55 us slower)
+static int row_blocks(int ninst) { return ninst == 1 ? 256 : std::min(256, std::max(1, 1024 / ninst)); }
+int rows_r2c_R(int nx, int ny, int ninst) {
   int R = 8;
   while (R > 2 && (R > ny || R * nx > 4096)) R >>= 1;
   while (R > 2 && 3 * (ny / R) < 256) R >>= 1;
+  // (more than a butterfly per thread is another way through the transform, and
+  // an instance's bits are those of the instance alone: not with more rows either)
+  if (ninst == 1 || R * nx > 2048) return R;
+  for (R = 16; R > 2 && (R > ny || R * nx > 2048 || 3 * (ny / R) < row_blocks(ninst));) R >>= 1;
   return R;
 }
-int rows_c2r_R(int nx, int ny) {
-  int R = 8;
+int rows_c2r_R(int nx, int ny, int ninst) {
+  int R = ninst == 1 ? 8 : 16;
   while (R > 1 && (R > ny || R * nx > 1024)) R >>= 1;
-  while (R > 2 && 6 * (ny / R) < 256) R >>= 1;
+  while (R > 2 && 6 * (ny / R) < row_blocks(ninst)) R >>= 1;
   return R;
 }
 // work buffers plus the staged twiddles (n complex entries)
-size_t rows_r2c_lds_bytes(int nx, int ny) { return (size_t)(rows_r2c_R(nx, ny) + 1) * nx * sizeof(double2); }
-size_t rows_c2r_lds_bytes(int nx, int ny) { return (size_t)(2 * rows_c2r_R(nx, ny) + 1) * nx * sizeof(double2); }
+size_t rows_r2c_lds_bytes(int nx, int R) { return (size_t)(R + 1) * nx * sizeof(double2); }
+size_t rows_c2r_lds_bytes(int nx, int R) { return (size_t)(2 * R + 1) * nx * sizeof(double2); }
 // inverse batch size of the column kernel and its LDS bytes (<= 160 KiB)
 int columns_nb(int ny) { return ny <= 256 ? 8 : (ny <= 512 ? 4 : 2); }
 // k_adj_columns: accumulators 4 ny, work buffers max(6, 2 nb) ny (bounded here

@@ -479,11 +479,11 @@ hipError_t launch_tiled(int dtype, int mode, int degree, int geo, const InstDesc
 
 // field.hip
 void fft_make_twiddles(int n, double* host_re_im);  // n complex entries
-int rows_r2c_R(int nx, int ny);
-int rows_c2r_R(int nx, int ny);
+int rows_r2c_R(int nx, int ny, int ninst);
+int rows_c2r_R(int nx, int ny, int ninst);
 int columns_nb(int ny);
-size_t rows_r2c_lds_bytes(int nx, int ny);
-size_t rows_c2r_lds_bytes(int nx, int ny);
+size_t rows_r2c_lds_bytes(int nx, int R);
+size_t rows_c2r_lds_bytes(int nx, int R);
 size_t adj_columns_lds_bytes(int ny);
 // blocks per kx of the forward column kernel (4 for BDF-k and CDF-2, split
 // by output; 1 for DIRK-2) and the split kernel's LDS bytes

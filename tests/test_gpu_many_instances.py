@@ -11,7 +11,7 @@ import pytest
 import torch
 
 from paper_2410_18414_amd import pic, workloads
-from pic_harness import compare_particles, gpu_parts, make_gpu, rel
+from pic_harness import make_gpu, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -44,5 +44,30 @@ def test_members_equal_instances_alone(gpu_lib, count, extra):
             d = (pa[k] - pb[k]).abs()
             box = (w["lx"], w["ly"])[k]
             assert torch.minimum(d, box - d).max().item() <= 1e-10 * box, (i, k)
+        a.close()
+    b.close()
+
+
+def test_row_groups_of_ensembles_keep_the_bits(gpu_lib):
+    """The row transforms of an ensemble take more rows per block than those of an
+    instance alone (up to 16, the last group partial): with the deterministic
+    deposit every member keeps the bits of the instance alone."""
+    sides = [(64, 97), (33, 100), (128, 50), (48, 112), (512, 48), (512, 16), (16, 96), (8, 49)]
+    ws = [workloads.cloud(nx=sides[i % 8][0], ny=sides[i % 8][1], ppc=1, seed=i, drift=0.2, vth=0.05) for i in range(64)]
+    flags = pic.FLAG_DETERMINISTIC
+    cfgs = [pic.make_config(w["nx"], w["ny"], w["lx"], w["ly"], w["dt"], degree=2, scheme="bdf", bdf_order=2,
+                            dtype="f32", q=w["q"], m=w["m"], max_particles=len(w["x"]), flags=flags) for w in ws]
+    b = pic.Context(cfgs)
+    for i, w in enumerate(ws):
+        pic.select_instance(b, i)
+        pic.init_particles(b, torch.as_tensor(w["x"], device=b.device), torch.as_tensor(w["y"], device=b.device),
+                           torch.as_tensor(np.ascontiguousarray(w["P"].T), device=b.device))
+    pic.step_batched(b, 6)
+    for i in list(range(8)) + [63]:
+        a = make_gpu(ws[i], 2, "bdf", "f32", bdf_order=2, flags=flags)
+        pic.step(a, 6)
+        pic.select_instance(b, i)
+        assert torch.equal(pic.get_history(b), pic.get_history(a)), i
+        assert torch.equal(pic.get_particles(b), pic.get_particles(a)), i
         a.close()
     b.close()
