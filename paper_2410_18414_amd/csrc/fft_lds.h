@@ -70,16 +70,16 @@ __device__ __forceinline__ void dft(double2 (&v)[R]) {
 // arithmetic and its two LDS round trips.  N = 128, two transforms: 1.04 us;
 // 1.24 us with run-time strides, 1.84 us with run-time divisions.  Radix 8 takes
 // fewer passes but gives the few busy waves three times the instructions: 1.7 us.
-// Transforms are pitch apart (0: 2^lN).  LOOP: any number of butterflies.
-template <bool INV, bool LOOP>
+// Transforms are pitch apart (0: 2^lN).
+template <bool INV>
 __device__ __forceinline__ double2* fft_pow2(double2* a, double2* b, const int lN, int B,
                                              const double2* __restrict__ tw, int pitch) {
-  const int lq = lN - 2, q = 1 << lq, nt = B << lq, step = LOOP ? blockDim.x : 1 << 30;
-  auto row = [&](int t) { return pitch ? (t >> lq) * pitch : (t >> lq) << lN; };
+  const int lq = lN - 2, q = 1 << lq, t = threadIdx.x;
+  const bool act = t < B << lq;
+  const int j = t & (q - 1), fo = pitch ? (t >> lq) * pitch : (t >> lq) << lN;
 #pragma unroll
   for (int ls = 0; ls + 2 <= lN; ls += 2) {
-    for (int t = threadIdx.x; t < nt; t += step) {
-      const int j = t & (q - 1), fo = row(t);
+    if (act) {
       const double2* x = a + fo + j;
       double2 v[4] = {x[0], x[q], x[2 * q], x[3 * q]};
       const int k = j & ((1 << ls) - 1);
@@ -102,8 +102,7 @@ __device__ __forceinline__ double2* fft_pow2(double2* a, double2* b, const int l
   }
   if (lN & 1) {  // two butterflies per thread
     const int h = 2 * q;
-    for (int t = threadIdx.x; t < nt; t += step) {
-      const int j = t & (q - 1), fo = row(t);
+    if (act) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const double2 w = tw[j + u * q];
@@ -223,33 +222,30 @@ __device__ __forceinline__ void fft_pass_odd(double2* a, double2* b, const FftPa
 }
 
 // B independent FFTs of the plan's length held in LDS at a[f*N + j] (f*pitch + j
-// if one is given; Stockham autosort: fft_pow2 for a power of two with one
-// butterfly per thread or up to 128 points, else the passes of the plan's
-// radices).  Ping-pongs between a and b and returns the buffer holding the result.  tw[t] = exp(-2 pi i t / N),
-// t < N.  INV: exp(+...) (unnormalised inverse).  All threads of the block must
-// call it; the caller synchronises before.
-template <bool INV, bool LOOP = false>
+// if a pitch is given; Stockham autosort: fft_pow2 for a power of two with one
+// butterfly per thread, else the passes of the plan's radices).  Ping-pongs
+// between a and b and returns the buffer holding the result.
+// tw[t] = exp(-2 pi i t / N), t < N.  INV: exp(+...) (unnormalised inverse).
+// MAXLN: log2 of the longest power of two that the caller transforms.  All
+// threads of the block must call it; the caller synchronises before.
+template <bool INV, int MAXLN = 10>
 __device__ __forceinline__ double2* fft_lds(double2* a, double2* b, const FftPlan& p, int B,
                                             const double2* __restrict__ tw, int pitch = 0) {
   const int N = p.n;
-  if constexpr (LOOP) {
+  if (B * N <= 4 * (int)blockDim.x) {
     switch (N) {
-      case 8: return fft_pow2<INV, true>(a, b, 3, B, tw, pitch);
-      case 16: return fft_pow2<INV, true>(a, b, 4, B, tw, pitch);
-      case 32: return fft_pow2<INV, true>(a, b, 5, B, tw, pitch);
-      case 64: return fft_pow2<INV, true>(a, b, 6, B, tw, pitch);
-      case 128: return fft_pow2<INV, true>(a, b, 7, B, tw, pitch);
+      case 8: return fft_pow2<INV>(a, b, 3, B, tw, pitch);
+      case 16: return fft_pow2<INV>(a, b, 4, B, tw, pitch);
+      case 32: return fft_pow2<INV>(a, b, 5, B, tw, pitch);
+      case 64: return fft_pow2<INV>(a, b, 6, B, tw, pitch);
+      case 128: return fft_pow2<INV>(a, b, 7, B, tw, pitch);
     }
-  } else if (B * N <= 4 * (int)blockDim.x) {
-    switch (N) {
-      case 8: return fft_pow2<INV, false>(a, b, 3, B, tw, pitch);
-      case 16: return fft_pow2<INV, false>(a, b, 4, B, tw, pitch);
-      case 32: return fft_pow2<INV, false>(a, b, 5, B, tw, pitch);
-      case 64: return fft_pow2<INV, false>(a, b, 6, B, tw, pitch);
-      case 128: return fft_pow2<INV, false>(a, b, 7, B, tw, pitch);
-      case 256: return fft_pow2<INV, false>(a, b, 8, B, tw, pitch);
-      case 512: return fft_pow2<INV, false>(a, b, 9, B, tw, pitch);
-      case 1024: return fft_pow2<INV, false>(a, b, 10, B, tw, pitch);
+    if constexpr (MAXLN > 7) {
+      switch (N) {
+        case 256: return fft_pow2<INV>(a, b, 8, B, tw, pitch);
+        case 512: return fft_pow2<INV>(a, b, 9, B, tw, pitch);
+        case 1024: return fft_pow2<INV>(a, b, 10, B, tw, pitch);
+      }
     }
   }
   FftPass s;

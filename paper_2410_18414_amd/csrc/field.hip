@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
 // kSmallCells: at 40 x 40 18.4 and 20.5, at 64 x 64 15.8 and 33 us.
 // The last of the four blocks to have read J clears it for the next deposit
 // (InstDesc::jread counts them; nobody waits).
-constexpr int kSmallCells = 1024, kSmallThreads = 768;  // a mode per thread: at most 5 x 128
+constexpr int kSmallCells = 1024, kSmallThreads = 768;  // a mode (at most 5 x 128) and a butterfly per thread
 
 // LDS: three buffers -- the spectra of a part's two outputs move between the
 // first two, then the rows of its three mesh fields between the free one and the
@@ -571,7 +571,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(const InstDesc* _
   // this block's reads of J are in LDS
   if (tid == 0) last = (__hip_atomic_fetch_add(d.jread, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 3) == 3;
 
-  const double2* z = fft_lds<false, true>(X, Y, d.fx, nb, twx);
+  const double2* z = fft_lds<false, 7>(X, Y, d.fx, nb, twx);
   double2* in = z == X ? Y : X;
   // the two rows of each transform, into columns
   for (int t = tid; t < nb * nxh; t += nth) {
@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(const InstDesc* _
     if (r1 < rows) in[(p1 * nxh + k) * pitch + r1 - p1 * ny] = make_double2(0.5 * dd.y, -0.5 * dd.x);
   }
   __syncthreads();
-  const double2* Jh = fft_lds<false, true>(in, in == X ? Y : X, d.fy, ncol * nxh, twy, pitch);
+  const double2* Jh = fft_lds<false, 7>(in, in == X ? Y : X, d.fy, ncol * nxh, twy, pitch);
   double2* G = Jh == X ? Y : X;  // the outputs' spectra: the field and its y derivative
   const double scale = 1.0 / ((double)nx * ny);
   if (tid < modes) {
@@ -597,7 +597,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(const InstDesc* _
     G[nxh * pitch + o] = mul_i(cscale(out, kys));
   }
   __syncthreads();
-  const double2* U = fft_lds<true, true>(G, G == X ? Y : X, d.fy, 2 * nxh, twy, pitch);
+  const double2* U = fft_lds<true, 7>(G, G == X ? Y : X, d.fy, 2 * nxh, twy, pitch);
   // the three mesh fields, pairs of rows
   double2* a = U == X ? Y : X;
   const int hy = (ny + 1) >> 1;
@@ -626,7 +626,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(const InstDesc* _
     if (k > 0 && k != nyq) a[row * nx + nx - k] = cadd(cconj(P), mul_i(cconj(Q)));
   }
   __syncthreads();
-  const double2* res = fft_lds<true, true>(a, Z, d.fx, 3 * hy, twx);
+  const double2* res = fft_lds<true, 7>(a, Z, d.fx, 3 * hy, twx);
   for (int t = tid; t < 3 * hy * nx; t += nth) {
     const int row = fdiv(t, inv_nx), x = t - row * nx;
     const int f = fdiv(row, inv_hy), y = 2 * (row - f * hy), s = slot_of(f);
