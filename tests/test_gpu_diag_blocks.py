@@ -36,3 +36,23 @@ def test_diagnostics_of_any_size(gpu_lib, nx, ny, n, scheme):
     for k in ("gauge_scale", "gauss_scale", "energy", "kinetic", "nonfinite"):
         assert abs(got[k] - both[k]) <= 1e-12 * abs(got[k]), k
     g.close()
+
+
+@pytest.mark.parametrize("n", [2 * 65536 - 1, 4 * 65536, 4 * 65536 + 1, 7 * 65536 + 129])
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_particle_sums_over_whole_and_partial_batches(gpu_lib, n, dtype):
+    """Four particles of a thread are loaded together: counts around one, two and
+    four strides of the full 256 blocks.  The kinetic energy against numpy's of
+    the exported velocities (n sums of positive terms: n 2^-53 < 1e-10)."""
+    print("case", n, dtype, flush=True)
+    w = workloads.weibel(nx=64, ny=64, ppc=-(-n // 4096), seed=5)
+    for k in ("x", "y", "P"):
+        w[k] = w[k][:n]
+    g = make_gpu(w, 2, "bdf", dtype)
+    pic.step(g, 2)
+    v = pic.get_particles(g)[5:8].cpu().numpy()
+    got = pic.diagnostics(g)
+    want = float(((1.0 / np.sqrt(1.0 - (v ** 2).sum(0)) - 1.0) * w["m"]).sum())
+    assert abs(got["kinetic"] - want) <= 1e-10 * want
+    assert got["nonfinite"] == 0
+    g.close()
