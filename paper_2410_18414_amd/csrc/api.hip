@@ -1456,8 +1456,8 @@ pic_status_t pic_get_field(pic_ctx_t c, int32_t which, double* dst) {
     if (c->phase != SOLVED) return c->fail(PIC_ERR_STATE, "mesh fields are valid in phase SOLVED");
     if (c->dtype == PIC_F32 && c->nblk[BK_C2R]) {
       // the step writes only the float32 copy: the float64 planes from the
-      // solve's spectra (U is valid until the next solve;
-      // the one-launch solve of a small grid writes both)
+      // solve's spectra (U is valid until the next solve and kept in saved
+      // states; the one-launch solve of a small grid writes both)
       pic_status_t st = c->hip(launch_rows_c2r(c->d_desc, c->ninst(), c->nblk[BK_C2R], c->lds_c2r, c->stream,
                                                false, true),
                                "mesh field export");
@@ -1550,13 +1550,19 @@ pic_status_t pic_set_dirk_tableau(pic_ctx_t c, int32_t stages, const double* A, 
 
 // byte offsets of one instance's parts inside a saved state
 struct StateLayout {
-  size_t parts, ids, start, cstart, work, nwork, hist, rb, fields, end;
+  size_t parts, ids, start, cstart, work, nwork, hist, rb, fields, mesh, end;
 };
 // the mesh fields the gather reads (float32 contexts: the node-major copy;
 // float64: the twelve planes), kept by states saved in phase SOLVED
 static size_t field_state_bytes(const Instance& in) {
   const size_t plane = (size_t)in.cfg.nx * in.cfg.ny;
   return in.d.F32 ? 12 * plane * 4 : 12 * plane * 8;
+}
+// float32 contexts, also in phase SOLVED: what PIC_FIELD_MESH is made of, the
+// solve's spectra or, after a one-launch solve, its float64 planes
+static size_t mesh_state_bytes(pic_ctx_t c, const Instance& in) {
+  if (!in.d.F32) return 0;
+  return c->nblk[BK_C2R] ? 8 * in.L.plane_c * 16 : (size_t)12 * in.cfg.nx * in.cfg.ny * 8;
 }
 static StateLayout state_layout(pic_ctx_t c, const Instance& in, size_t base) {
   StateLayout L{};
@@ -1577,6 +1583,7 @@ static StateLayout state_layout(pic_ctx_t c, const Instance& in, size_t base) {
   L.hist = take((size_t)c->hist.nslots * in.L.plane_c * 16);
   L.rb = take(in.d.RB ? (size_t)in.cfg.nx * in.cfg.ny * 8 : 0);
   L.fields = take(field_state_bytes(in));
+  L.mesh = take(mesh_state_bytes(c, in));
   L.end = o;
   return L;
 }
@@ -1627,6 +1634,7 @@ static std::vector<std::array<size_t, 3>> state_segments(pic_ctx_t c, int cur, c
     seg.push_back({L.hist, (size_t)d.H, (size_t)c->hist.nslots * in.L.plane_c * 16});
     if (d.RB) seg.push_back({L.rb, (size_t)d.RB, (size_t)in.cfg.nx * in.cfg.ny * 8});
     if (solved) seg.push_back({L.fields, d.F32 ? (size_t)d.F32 : (size_t)d.F64, field_state_bytes(in)});
+    if (solved && d.F32) seg.push_back({L.mesh, c->nblk[BK_C2R] ? (size_t)d.U : (size_t)d.F64, mesh_state_bytes(c, in)});
     o = L.end;
   }
   return seg;

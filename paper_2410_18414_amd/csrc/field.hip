@@ -438,9 +438,9 @@ __constant__ int kMulKx[12] = {1, 0, 0, 0, 0, 1, 1, 1, 0, 0, 0, 0};
 //
 // adj: the three columns LS[0..2] of the adjoint solve to the real fields LJ
 // (pairs (0, 1) and (2, -); no kx factor).
-// f64out: also write the float64 planes (always for float64 particles and the
-// adjoint; float32 contexts read only the node-major float32 copy, and their
-// float64 planes are written on demand for the mesh-field export)
+// Float64 contexts and the adjoint write the float64 planes.  A float32 step
+// writes only the node-major float32 copy its particles read; f64out: only its
+// float64 planes, for the mesh-field export (what the particles read stays).
 __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D, int ninst, int adj, int f64out) {
   extern __shared__ double2 sm[];
   // the pairs of one row group in consecutive blocks, and neighbouring blocks
@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
   const int nr = min(R, g.ny - y0);  // rows of this group (the last may be partial)
   const GC2 U = gc2(adj ? d.LS : d.U);
   const gptr<double> F64 = gp(adj ? d.LJ : d.F64);
-  const gptr<float> F32 = gp(adj ? nullptr : d.F32);
+  const gptr<float> F32 = gp(adj || f64out ? nullptr : d.F32);
   const int N = g.nx;
   const int nyq = (N & 1) ? -1 : N >> 1;  // Nyquist bin (even nx only)
   double2* a = sm;
@@ -495,13 +495,12 @@ __global__ void __launch_bounds__(256) k_rows_c2r(const InstDesc* __restrict__ D
     const int r = fdiv(t, d.fx.inv_n), x = t - r * N;
     const size_t o = (size_t)(y0 + r) * N + x;
     const double2 z = res[t];
-    if (f64out || !F32) {
-      F64[s0 * plane + o] = z.x;
-      if (has1) F64[s1 * plane + o] = z.y;
-    }
     if (F32) {  // node-major record: slots s0, s0 + 1 of node o
       F32[o * kFieldSlots + s0] = (float)z.x;
       F32[o * kFieldSlots + s0 + 1] = (float)z.y;
+    } else {
+      F64[s0 * plane + o] = z.x;
+      if (has1) F64[s1 * plane + o] = z.y;
     }
   }
 }
