@@ -1737,7 +1737,21 @@ pic_status_t pic_load_state_h(pic_ctx_t c, const void* src, const int64_t* heade
   if (cur != 0 && cur != 1) return c->fail(PIC_ERR_INVALID_ARG, "src holds an invalid particle set index");
   if (h[11] != 0 && h[11] != 1) return c->fail(PIC_ERR_INVALID_ARG, "src holds an invalid phase");
   const bool solved = h[11] == 1;
-  st = copy_segments(c, state_segments(c, cur, ns, solved), const_cast<char*>(b), false);
+  // J is zero in the phases a state is saved in; a deposit that no solve has
+  // read, or what a failed call left, does not survive the load
+  if (c->phase != READY && c->phase != SOLVED)
+    for (const Instance& in : c->inst) {
+      const size_t plane = (size_t)in.cfg.nx * in.cfg.ny;
+      if (!st) st = c->hip(launch_fill_f64(in.d.J, j_planes(in.d.sc, 0) * plane, 0.0, c->stream), "J fill");
+      if (!st && in.d.LF) st = c->hip(launch_fill_f64(in.d.LF, 11 * plane, 0.0, c->stream), "adjoint fill");
+    }
+  if (!st) st = copy_segments(c, state_segments(c, cur, ns, solved), const_cast<char*>(b), false);
+  for (const Instance& in : c->inst) {  // the naive mode's rho plane starts from the state's ion background
+    const size_t plane = (size_t)in.cfg.nx * in.cfg.ny;
+    if (!st && in.d.RB)
+      st = c->hip(hipMemcpyAsync(in.d.J + 3 * plane, in.d.RB, plane * 8, hipMemcpyDeviceToDevice, c->stream),
+                  "rho plane start");
+  }
   if (st) {
     c->phase = EMPTY;
     return st;
