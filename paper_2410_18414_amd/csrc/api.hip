@@ -197,6 +197,21 @@ int chunk_base(int64_t n) {
   while (base < 4096 && n / (2 * base) >= 8192) base *= 2;
   return base;
 }
+// The tiles of a plan by extent (full, and partial at the high edges): how many,
+// their expected particles, and those with four standard deviations of margin
+struct TileKind {
+  double count, mean, most;
+};
+std::array<TileKind, 4> tile_kinds(const pic_config_t& c, const TileP& t) {
+  const int fx = c.nx / t.ts, fy = c.ny / t.ts, rx = c.nx - fx * t.ts, ry = c.ny - fy * t.ts;
+  const double per_cell = (double)c.max_particles / ((double)c.nx * c.ny);
+  auto kind = [&](int count, int w, int h) {
+    const double k = per_cell * w * h;
+    return TileKind{(double)count, k, k + 4.0 * std::sqrt(k)};
+  };
+  return {kind(fx * fy, t.ts, t.ts), kind(rx ? fy : 0, rx, t.ts), kind(ry ? fx : 0, ry, t.ts),
+          kind(rx && ry ? 1 : 0, rx, ry)};
+}
 int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
   const int64_t n = c.max_particles;
   const int base = chunk_base(n);
@@ -205,24 +220,17 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
   const size_t lds = tiled_lds_bytes(c.particle_dtype, 2, t, (c.flags & PIC_FLAG_NAIVE_RHO) != 0);
   const double per_cu = (double)std::max<size_t>(1, std::min<size_t>(4, 163840 / lds));
   const double slots = 256.0 * per_cu * ((double)n / (double)total);
-  // tiles by extent (full, and partial at the high edges), with four standard
-  // deviations of margin on their expected particles
-  const int fx = c.nx / t.ts, fy = c.ny / t.ts, rx = c.nx - fx * t.ts, ry = c.ny - fy * t.ts;
-  const double per_cell = (double)n / ((double)c.nx * c.ny);
-  const double tiles[4][2] = {{(double)fx * fy, per_cell * t.ts * t.ts},
-                              {rx ? (double)fy : 0.0, per_cell * rx * t.ts},
-                              {ry ? (double)fx : 0.0, per_cell * ry * t.ts},
-                              {rx && ry ? 1.0 : 0.0, per_cell * rx * ry}};
+  const auto tiles = tile_kinds(c, t);
   const double fixed = f32 ? 1.2 : 2.2;
   int best = base;
   double best_cost = 1e300;
   for (int chunk = 256; chunk < (f32 ? 2 * base : 8192); chunk += 16) {
     double items = 0.0, iters = 0.0;
     for (const auto& k : tiles) {
-      if (k[0] == 0.0) continue;
-      const double parts = std::ceil((k[1] + 4.0 * std::sqrt(k[1])) / chunk);
-      items += k[0] * parts;
-      const double size = k[1] / parts + std::sqrt(k[1]) / parts, whole = std::floor(size / 256.0);
+      if (k.count == 0.0) continue;
+      const double parts = std::ceil(k.most / chunk);
+      items += k.count * parts;
+      const double size = (k.mean + 0.25 * (k.most - k.mean)) / parts, whole = std::floor(size / 256.0);
       const double part = size / 256.0 - whole;
       iters = std::max(iters, whole + (part > 0.0 && f32 ? std::max(0.7, part) : part));
     }
@@ -271,6 +279,12 @@ TileP plan_tiles(const pic_config_t& c, int64_t total) {
   }
   t.chunk = c.chunk ? c.chunk : plan_chunk(c, t, total);
   t.max_work = t.ntiles + ceil_div(c.max_particles, t.chunk);
+  t.main_work = t.max_work;
+  if (c.max_particles < total) {
+    double items = 0.0;
+    for (const TileKind& k : tile_kinds(c, t)) items += k.count * std::ceil(k.most / t.chunk);
+    t.main_work = (int)std::min<double>(items, t.max_work);
+  }
   t.log_group = 0;
   while ((t.ntiles - 1) >> t.log_group >= kMaxBuckets) t.log_group++;
   return t;
@@ -622,7 +636,7 @@ struct pic_ctx_s {
   }
   int ninst() const { return (int)inst.size(); }
   Instance& I() { return inst[sel]; }
-  StepArgs sargs(int stage = -1) const { return StepArgs{cur, vflip, stage}; }
+  StepArgs sargs(int stage = -1) const { return StepArgs{cur, vflip, stage, nblk[BK_WORK]}; }
 
   // fold pending pairs into the totals (synchronises the stream)
   hipError_t fold_timing() {
@@ -741,8 +755,8 @@ pic_status_t particle_pass(pic_ctx_t c, int mode, bool may_sort = true) {
   const int nst = mode == 0 && sc.substep ? sc.stages : 0;
   hipError_t e = hipSuccess;
   for (int k = nst ? 0 : -1; k < nst && e == hipSuccess; ++k)
-    e = c->sorted ? launch_tiled(c->dtype, mode, c->degree, c->geo, c->d_desc, c->ninst(), c->nblk[BK_WORK],
-                                 c->lds_tiled[mode], c->sargs(k), c->stream)
+    e = c->sorted ? launch_tiled(c->dtype, mode, c->degree, c->geo, c->d_desc, c->ninst(),
+                                 c->nblk[BK_WORK] + c->nblk[BK_MORE], c->lds_tiled[mode], c->sargs(k), c->stream)
                   : launch_untiled(c->dtype, mode, c->degree, c->d_desc, c->ninst(), c->nblk[BK_PART], c->sargs(k),
                                    c->stream);
   c->end_timed(t);
@@ -1018,11 +1032,12 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     // flattened block ranges
     const int nb[BK_NKINDS] = {small ? 0 : ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
                                small ? 0 : (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
-                               small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
+                               small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.main_work,
                                ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 256 * c->count_items),
                                ceil_div(d.tp.ntiles, 4),
                                ceil_div(cf.max_particles, kSplitWidth * c->split_items),
-                               small ? columns_parts(scheme_family(cf.scheme)) : 0};
+                               small ? columns_parts(scheme_family(cf.scheme)) : 0,
+                               d.tp.max_work - d.tp.main_work};
     for (int k = 0; k < BK_NKINDS; ++k) {
       d.blk[k] = c->nblk[k];
       c->nblk[k] += nb[k];
