@@ -190,7 +190,10 @@ bool compatible(const pic_config_t& a, const pic_config_t& b, std::string& msg) 
 // few: 53, 683: 44.6, 910: 43.7; 64 x 64 with 32768 float64 256: 10.6, 512: 13.5.
 // Float32 candidates stay below twice the power of two (512 .. 4096, the largest
 // that leaves 8192 chunks) that fixes the deposit's scale.  Sets of at most 8192
-// particles take chunks of 128 (9.4 us instead of 13.2 with 4096 particles).
+// particles take chunks of 128 while those leave a workgroup per CU (9.4 us instead
+// of 13.2 with 4096 particles); beyond, half of a workgroup's lanes would idle and
+// its window be loaded for half as many (step of 1024 members of 16 x 16 with 4096
+// particles, float32 and float64: 343 and 1004 us with 128, 212 and 286 as planned).
 // An instance of an ensemble has its share (by particles, total) of the slots.
 int chunk_base(int64_t n) {
   int base = 512;
@@ -216,7 +219,7 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
   const int64_t n = c.max_particles;
   const int base = chunk_base(n);
   const bool f32 = c.particle_dtype == PIC_F32;
-  if (n <= 8192) return 128;
+  if (n <= 8192 && total <= 128 * 256) return 128;
   const size_t lds = tiled_lds_bytes(c.particle_dtype, 2, t, (c.flags & PIC_FLAG_NAIVE_RHO) != 0);
   const double per_cu = (double)std::max<size_t>(1, std::min<size_t>(4, 163840 / lds));
   const double slots = 256.0 * per_cu * ((double)n / (double)total);
