@@ -1,10 +1,10 @@
 """Tile-plan autotuner for the cell-sorted particle passes.
 
 The tiled passes have four knobs (pic_config_t): the tile edge in cells
-(`tile_cells`), the particles per workgroup (`chunk`), the steps between
-re-sorts (`sort_interval`) and whether step() fuses the gather/push with the
-next deposit (PIC_FLAG_UNFUSED_STEP).  Their
-best values depend on the grid, the particles per cell and the particle
+(`tile_cells`), the particles per workgroup (`chunk`; 0: the library's own
+plan, per instance), the steps between re-sorts (`sort_interval`) and whether
+step() fuses the gather/push with the next deposit (PIC_FLAG_UNFUSED_STEP).
+Their best values depend on the grid, the particles per cell and the particle
 precision, so they are measured: every candidate plan runs a few steps of the
 caller's own workload (warm-up steps first, so the first sort and the graph
 capture stay out of the timing), timed with HIP events on the context's
@@ -31,7 +31,7 @@ from . import pic
 # correct -- particles that leave their window take the global path -- and pay
 # off when particles are slower than c)
 CANDIDATES = [dict(tile_cells=t, chunk=c, unfused=u, sort_interval=si)
-              for t in (8, 16) for c in (512, 1024, 2048, 4096) for u in (False, True) for si in (0, 12)]
+              for t in (8, 16) for c in (0, 512, 1024, 2048, 4096) for u in (False, True) for si in (0, 12)]
 KNOBS = ("tile_cells", "chunk", "unfused", "sort_interval")
 
 
