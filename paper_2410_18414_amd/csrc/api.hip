@@ -227,11 +227,13 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
   const double fixed = f32 ? 1.2 : 2.2;
   int best = base;
   double best_cost = 1e300;
-  for (int chunk = 256; chunk < (f32 ? 2 * base : 8192); chunk += 16) {
-    double items = 0.0, iters = 0.0;
+  // (in steps of 16, but for those that split every tile into as many parts as the last)
+  for (int chunk = 256, next = 0; chunk < (f32 ? 2 * base : 8192); chunk = next) {
+    double items = 0.0, iters = 0.0, fewer = 8192.0;
     for (const auto& k : tiles) {
       if (k.count == 0.0) continue;
       const double parts = std::ceil(k.most / chunk);
+      if (parts > 1.0) fewer = std::min(fewer, k.most / (parts - 1.0));
       items += k.count * parts;
       const double size = (k.mean + 0.25 * (k.most - k.mean)) / parts, whole = std::floor(size / 256.0);
       const double part = size / 256.0 - whole;
@@ -247,6 +249,8 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
       best_cost = cost;
       best = chunk;
     }
+    next = std::max(chunk, (int)fewer & ~15);
+    if (next == chunk) next += 16;
   }
   return best;
 }
@@ -341,8 +345,8 @@ Layout plan_instance(const pic_config_t& c, int64_t total) {
   L.twork = take((size_t)tp.max_work * 16);
   L.tnwork = take(4);
   L.tdone = take(8);  // and InstDesc::jread
+  L.tbucket = take((size_t)2 * kMaxBuckets * 4);  // cleared together with those
   L.trank = take((size_t)cap * 4);
-  L.tbucket = take((size_t)2 * kMaxBuckets * 4);
   if (c.flags & PIC_FLAG_ADJOINT) {
     L.LF = take(11 * plane_r * 8);
     L.LS = take(11 * L.plane_c * 16);
@@ -1070,8 +1074,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     }
     if (e == hipSuccess) e = hipMemset(d.tb.count, 0, (size_t)d.tp.ntiles * 4);
     if (e == hipSuccess) e = hipMemset(d.tb.ccount, 0, (size_t)d.tp.ntiles * d.tp.ts * d.tp.ts * 4);
-    if (e == hipSuccess) e = hipMemset(d.tb.done, 0, 8);
-    if (e == hipSuccess) e = hipMemset(d.tb.bcount, 0, kMaxBuckets * 4);
+    if (e == hipSuccess) e = hipMemset(d.tb.done, 0, (char*)(d.tb.bcount + kMaxBuckets) - (char*)d.tb.done);
   }
   c->sort_every = every;
   c->geo = tiled_geometry(c->inst[0].d.tp);

@@ -7,6 +7,7 @@ alone and few members do, members of a large ensemble take longer chunks, as
 larger members do."""
 
 import ctypes
+import time
 
 import pytest
 
@@ -30,3 +31,21 @@ def test_chunks_of_128_leave_at_most_a_workgroup_per_cu(count, nx, n, short, dty
         assert planned == small
     else:
         assert planned < small
+
+
+def test_planning_an_ensemble_is_quick():
+    """A program pays for the plan of every member when it makes a context: at most
+    10 times the sums of the workspace with a chunk given (3.6 as it is, 27 when
+    every size in steps of 16 was priced)."""
+    best = []
+    for chunk in (0, 1024):
+        cfg = pic.make_config(24, 24, 2.4, 2.4, 0.02, dtype="f64", max_particles=9000, chunk=chunk)
+        arr = (pic.ConfigStruct * 1024)(*[cfg] * 1024)
+        times = []
+        for _ in range(9):
+            t = time.perf_counter()
+            assert pic.load().pic_batch_workspace_bytes(arr, ctypes.c_int32(1024)) > 0
+            times.append(time.perf_counter() - t)
+        best.append(min(times))
+    print("ratio", best[0] / best[1], best)
+    assert best[0] <= 10 * best[1]
