@@ -286,12 +286,6 @@ TileP plan_tiles(const pic_config_t& c, int64_t total) {
   }
   t.chunk = c.chunk ? c.chunk : plan_chunk(c, t, total);
   t.max_work = t.ntiles + ceil_div(c.max_particles, t.chunk);
-  t.main_work = t.max_work;
-  if (c.max_particles < total) {
-    double items = 0.0;
-    for (const TileKind& k : tile_kinds(c, t)) items += k.count * std::ceil(k.most / t.chunk);
-    t.main_work = (int)std::min<double>(items, t.max_work);
-  }
   t.log_group = 0;
   while ((t.ntiles - 1) >> t.log_group >= kMaxBuckets) t.log_group++;
   return t;
@@ -643,7 +637,7 @@ struct pic_ctx_s {
   }
   int ninst() const { return (int)inst.size(); }
   Instance& I() { return inst[sel]; }
-  StepArgs sargs(int stage = -1) const { return StepArgs{cur, vflip, stage, nblk[BK_WORK]}; }
+  StepArgs sargs(int stage = -1) const { return StepArgs{cur, vflip, stage}; }
 
   // fold pending pairs into the totals (synchronises the stream)
   hipError_t fold_timing() {
@@ -724,11 +718,12 @@ pic_status_t do_sort(pic_ctx_t c) {
   int64_t n = 0;
   for (const Instance& in : c->inst) n += in.d.n;
   const bool first = !c->from_sort && n >= kFirstSortMin;
-  const hipError_t e =
+  hipError_t e =
       first ? launch_first_sort(c->dtype, c->d_desc, c->ninst(), c->split_items, c->nblk[BK_SPLIT], c->nblk[BK_TILES],
                                 c->cur, c->stream)
             : launch_tile_sort(c->dtype, c->d_desc, c->ninst(), c->count_items, c->nblk[BK_COUNT], c->nblk[BK_TILES],
                                c->nblk[BK_PART], c->cur, c->stream);
+  if (e == hipSuccess && c->ninst() > 1) e = launch_work_first(c->d_desc, c->ninst(), c->stream);
   c->end_timed(t);
   pic_status_t st = c->hip(e, "tile sort");
   if (st) return st;
@@ -762,8 +757,8 @@ pic_status_t particle_pass(pic_ctx_t c, int mode, bool may_sort = true) {
   const int nst = mode == 0 && sc.substep ? sc.stages : 0;
   hipError_t e = hipSuccess;
   for (int k = nst ? 0 : -1; k < nst && e == hipSuccess; ++k)
-    e = c->sorted ? launch_tiled(c->dtype, mode, c->degree, c->geo, c->d_desc, c->ninst(),
-                                 c->nblk[BK_WORK] + c->nblk[BK_MORE], c->lds_tiled[mode], c->sargs(k), c->stream)
+    e = c->sorted ? launch_tiled(c->dtype, mode, c->degree, c->geo, c->d_desc, c->ninst(), c->nblk[BK_WORK],
+                                 c->lds_tiled[mode], c->sargs(k), c->stream)
                   : launch_untiled(c->dtype, mode, c->degree, c->d_desc, c->ninst(), c->nblk[BK_PART], c->sargs(k),
                                    c->stream);
   c->end_timed(t);
@@ -1039,12 +1034,11 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     // flattened block ranges
     const int nb[BK_NKINDS] = {small ? 0 : ceil_div(cf.ny, d.R_r2c) * j_planes(d.sc, d.naive),
                                small ? 0 : (cf.nx / 2 + 1) * columns_parts(scheme_family(cf.scheme)),
-                               small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.main_work,
+                               small ? 0 : ceil_div(cf.ny, d.R_c2r) * 6, d.tp.max_work,
                                ceil_div(cf.max_particles, 256), ceil_div(cf.max_particles, 256 * c->count_items),
                                ceil_div(d.tp.ntiles, 4),
                                ceil_div(cf.max_particles, kSplitWidth * c->split_items),
-                               small ? columns_parts(scheme_family(cf.scheme)) : 0,
-                               d.tp.max_work - d.tp.main_work};
+                               small ? columns_parts(scheme_family(cf.scheme)) : 0};
     for (int k = 0; k < BK_NKINDS; ++k) {
       d.blk[k] = c->nblk[k];
       c->nblk[k] += nb[k];
@@ -1792,8 +1786,12 @@ pic_status_t pic_load_state_h(pic_ctx_t c, const void* src, const int64_t* heade
   c->from_sort = h[10] != 0;
   c->adjoined = h[12] != 0;
   c->phase = solved ? SOLVED : READY;
-  // the device descriptors change only with the particle counts
-  return counts_changed ? c->upload_desc() : PIC_OK;
+  // the device descriptors change with the particle counts and, in an ensemble,
+  // with the chunk counts
+  if (counts_changed) st = c->upload_desc();
+  if (!st && c->sorted && ni > 1) st = c->hip(launch_work_first(c->d_desc, ni, c->stream), "chunk ranges");
+  if (st) c->phase = EMPTY;
+  return st;
 }
 
 pic_status_t pic_load_state(pic_ctx_t c, const void* src) { return pic_load_state_h(c, src, nullptr); }

@@ -225,7 +225,6 @@ struct TileP {
   int log_row_lanes;
   int chunk;       // max particles per workgroup
   int max_work;    // ntiles + ceil(capacity/chunk): bound on the chunk count
-  int main_work;   // chunks of uniformly placed particles (an instance alone: max_work)
   int pow2;        // 1: nx and ny are powers of two (node indices wrap by masks)
   int log_group;   // 2^log_group neighbouring tiles form a bucket of the first sort (at most kMaxBuckets)
 };
@@ -315,14 +314,13 @@ enum BlockKind {
   BK_R2C = 0,    // (ny/R_r2c) x 3 blocks (this and the next two: none where solve_small)
   BK_COL = 1,    // nxh x columns_parts(scheme) blocks
   BK_C2R = 2,    // (ny/R_c2r) x 6 blocks
-  BK_WORK = 3,   // tp.main_work blocks (tiled particle pass: the chunks in use, as a rule)
+  BK_WORK = 3,   // tp.max_work blocks (tiled particle pass; in an ensemble k_work_first moves the ranges)
   BK_PART = 4,   // ceil(capacity/256) blocks (untiled passes, scatter)
   BK_COUNT = 5,  // ceil(capacity/(256 count_items)) blocks (tile counting)
   BK_TILES = 6,  // ceil(ntiles/4) blocks (per-tile cell scan, one wave per tile)
   BK_SPLIT = 7,  // ceil(capacity/(kSplitWidth split_items)) blocks (bucket split)
   BK_SMALL = 8,  // 4 blocks where the whole solve is one launch (solve_small), else none
-  BK_MORE = 9,   // tp.max_work - tp.main_work blocks (tiled particle pass: the other chunks)
-  BK_NKINDS = 10
+  BK_NKINDS = 9
 };
 
 // One instance of the method: static for the life of a context.
@@ -371,7 +369,6 @@ struct StepArgs {
   int stage;  // deposit passes: -1 = x^{n+1} and J^{n+1}; i >= 0 = DIRK stage i of the
               // sub-stepped currents (deposit at x + c_i dt v into J planes 3i..3i+2;
               // the last stage also writes x^{n+1})
-  int more;   // tiled passes: first block of the chunks beyond main_work (BK_MORE)
 };
 
 // real J planes of an instance: 3, a fourth (the naive mode's rho), or three per DIRK stage
@@ -465,6 +462,7 @@ size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
 hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int count_items, int nb_count, int nb_tiles, int nb_part,
                             int src_set, hipStream_t s);
 hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s);
+hipError_t launch_work_first(InstDesc* D, int ninst, hipStream_t s);
 // reorder.hip: the sort of sets in no known order (src -> src, by way of
 // src ^ 1, every instance), and one instance's set src to out in original order
 // (by way of the set src ^ 1, split_parts)

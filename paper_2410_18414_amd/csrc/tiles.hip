@@ -262,6 +262,43 @@ __global__ void __launch_bounds__(kThreads) k_cell_scan(const InstDesc* __restri
   if (threadIdx.x == 0) *d.tb.done = 0;  // ready for the next sort
 }
 
+// Block ranges of the tiled passes of an ensemble after a sort (one workgroup): an
+// instance's chunks follow those of the one before it, and the blocks that no chunk is
+// left for come last.  In ranges of max_work blocks, which hold any chunk count, those
+// without a chunk (every second one, with one chunk per tile) repeat with the
+// instances, and whole XCDs and shader engines stay idle: a step of 64 members of 64 x
+// 64 with 65536 float64 particles 454 us, this way 281.  An instance of one tile gets an
+// odd range (its chunks are fewer than max_work, so there is a block to spare): with
+// eight chunks per instance the same part of each came to one XCD (1024 members of 16 x
+// 16, eight float64 chunks each: step 768 us, this way 480; of the members above, with
+// sixteen tiles, 315).
+__global__ void __launch_bounds__(kThreads) k_work_first(InstDesc* D, int ninst) {
+  __shared__ int32_t sums[kThreads / 64];
+  int* first = reinterpret_cast<int*>(D + ninst) + BK_WORK * ninst;  // as find_inst reads them
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int carry = 0;
+  for (int base = 0; base < ninst; base += kThreads) {
+    const int i = base + threadIdx.x;
+    const int n = i < ninst ? *gp((const int32_t*)D[i].tb.nwork) | (D[i].tp.ntiles == 1 ? 1 : 0) : 0;
+    int v = n;  // inclusive scans over the wave, then over the waves
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int u = __shfl_up(v, off);
+      if (lane >= off) v += u;
+    }
+    if (lane == 63) sums[wave] = v;
+    __syncthreads();
+    int before = carry;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+      before += w < wave ? sums[w] : 0;
+      carry += sums[w];
+    }
+    if (i < ninst) D[i].blk[BK_WORK] = first[i] = before + v - n;
+    __syncthreads();
+  }
+}
+
 // scatter set `src` into set `src ^ 1`, grouped by cell: particle i goes to its
 // tile's start + its cell's offset in the tile + its slot in the cell (from the
 // count pass); no atomics, so the copy streams.  The source is in the previous
@@ -332,15 +369,9 @@ __global__ void __launch_bounds__(kThreads) k_tiled(const InstDesc* __restrict__
   constexpr int TE = TS < 0 ? -TS : TS;  // compiled tile edge
   using G = Geo<(FIXED ? TE : 1), (FIXED ? SL : 0)>;
   using A = typename Acc<T>::type;
-  // An instance's chunk count is known on the device alone, and up to half of its
-  // max_work blocks have none.  Those of an ensemble come last: among the others they
-  // would repeat with the members, and whole XCDs and shader engines would stay idle
-  // (64 members of 64 x 64 with 65536 float64 particles: 311 us, this way 173)
-  const bool more = (int)blockIdx.x >= sa.more;
-  const int kind = more ? BK_MORE : BK_WORK, bb = blockIdx.x - (more ? sa.more : 0);
-  const int ii = find_inst(D, ninst, kind, bb);
+  const int ii = find_inst(D, ninst, BK_WORK, blockIdx.x);
   const InstDesc& d = D[ii];
-  const int item = bb - d.blk[kind] + (more ? d.tp.main_work : 0);
+  const int item = blockIdx.x - d.blk[BK_WORK];
   if (item >= *gp(d.tb.nwork)) return;
   const i32x4 itv = *reinterpret_cast<gptr<const i32x4>>(gp(d.tb.work + item));
   const int4 it = make_int4(itv.x, itv.y, itv.z, itv.w);
@@ -851,6 +882,11 @@ hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int count_i
 
 hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s) {
   hipLaunchKernelGGL(k_cell_scan, dim3(nb_tiles), dim3(kThreads), 0, s, D, ninst);
+  return hipGetLastError();
+}
+
+hipError_t launch_work_first(InstDesc* D, int ninst, hipStream_t s) {
+  hipLaunchKernelGGL(k_work_first, dim3(1), dim3(kThreads), 0, s, D, ninst);
   return hipGetLastError();
 }
 
