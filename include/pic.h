@@ -209,7 +209,9 @@ pic_status_t step(pic_ctx_t ctx, int32_t nsteps);
 int32_t pic_graph_period(pic_ctx_t ctx);
 
 /* Particle state in the ORIGINAL particle order, float64 device out[11 n]:
- * blocks x, y, Px, Py, Pz, vx^n, vy^n, vz^n, vx^{n-1}, vy^{n-1}, vz^{n-1}. */
+ * blocks x, y, Px, Py, Pz, vx^n, vy^n, vz^n, vx^{n-1}, vy^{n-1}, vz^{n-1}.
+ * Large sets (2^19 particles on) go by way of the workspace's second particle
+ * set, which holds nothing between sorts: the call writes to the workspace. */
 pic_status_t pic_get_particles(pic_ctx_t ctx, double* out);
 /* Replace the particle state (same layout, original order) in phase READY or
  * SOLVED; phase -> READY.  Values are rounded to the particle dtype; positions
@@ -220,7 +222,8 @@ pic_status_t pic_set_particles(pic_ctx_t ctx, const double* in);
  * (every instance's particles in their current sorted order with their
  * original indices, the tile metadata of the last sort, the spectral history
  * ring, the step, ring and sort counters, and in phase SOLVED the mesh fields
- * of the last solve), in a caller-owned DEVICE buffer of
+ * of the last solve, as the particles gather them and as PIC_FIELD_MESH gives
+ * them), in a caller-owned DEVICE buffer of
  * pic_state_bytes(ctx) bytes, 256-byte aligned.  pic_save_state enqueues
  * device-to-device copies (no synchronisation, no allocation); pic_load_state
  * restores a state saved by a context of the same configuration (it reads
@@ -322,8 +325,9 @@ pic_status_t pic_diagnostics_all(pic_ctx_t ctx, double* out);
 
 /* ---- Ensembles (batched instances) ----------------------------------------
  * A context may hold ninst independent instances of the method: an ensemble
- * of uneven workloads (different grids, particle counts, time steps).  They must share scheme, bdf_order, particle_dtype, spline_degree,
- * flags and c, eps0, mu0.  Every hot-path kernel then covers all instances in
+ * of uneven workloads (different grids, particle counts, time steps).  They
+ * must share scheme, bdf_order, particle_dtype, spline_degree, flags and c,
+ * eps0, mu0.  Every hot-path kernel then covers all instances in
  * one launch per phase (a flattened grid), and the instances advance in
  * lockstep: deposit_current, field_solve, gather_push, step and step_batched
  * act on all of them.  init_particles, pic_get/set_particles, pic_get_field,

@@ -52,11 +52,10 @@ struct LamRef {
 };
 
 // Push adjoint of one particle: gathered values gv at x^{n+1}; P^n, v^n,
-// v^{n-1}; lambda^{n+1} in lam in, lambda of P, v^n and v^{n-1} out.  Returns
-// l: the particle's adjoint values as loaded.  Returns
-// lambda_g in lg[11]: the callers scatter it onto the mesh fields and add the
-// gather's position term, sum_f lg[f] d gv[f] / dx, to lambda_x (and the same
-// for y).
+// v^{n-1}; lambda^{n+1} in l, the particle's adjoint values as loaded.  Writes
+// lambda of P, v^n and v^{n-1} through lam and returns lambda_g in lg[11]: the
+// callers scatter it onto the mesh fields and add the gather's position term,
+// sum_f lg[f] d gv[f] / dx, to lambda_x (and the same for y).
 __device__ __forceinline__ void adj_push_one(const double* gv, double P0, double P1, double P2, double v0, double v1,
                                              double v2, double w0, double w1, double w2, const PhysP& ph,
                                              const double* l, const LamRef& lam, double* lg) {

@@ -182,8 +182,9 @@ bool compatible(const pic_config_t& a, const pic_config_t& b, std::string& msg) 
 // uniformly placed particles.  A tile's chunks have equal sizes.  A workgroup
 // costs its window load and flush, about 1.2 iterations of its 256 lanes (2.2 in
 // float64, whose windows are twice as large), and its iterations, in float32 a
-// partly filled one nearly as much as a full one; the chip holds `slots` workgroups (by LDS four float32 or two float64 ones per CU), and
-// about half a workgroup's time passes before the last ones end.  Measured
+// partly filled one nearly as much as a full one; the chip holds `slots` workgroups
+// (by LDS four float32 or two float64 ones per CU), and about half a workgroup's
+// time passes before the last ones end.  Measured
 // (fused pass, us, by particles per chunk): 128 x 128 with 1M float32 particles
 // 497: 33.0, 512 and a few: 35.6, 683: 32.2, 964: 33.2; float64 497: 70, 683:
 // 65, 1024: 64, 1365: 61, 2048: 60, 2731: 73; 256 x 256 with 2M float32 482: 46, 512 and a
@@ -195,6 +196,9 @@ bool compatible(const pic_config_t& a, const pic_config_t& b, std::string& msg) 
 // its window be loaded for half as many (step of 1024 members of 16 x 16 with 4096
 // particles, float32 and float64: 343 and 1004 us with 128, 212 and 286 as planned).
 // An instance of an ensemble has its share (by particles, total) of the slots.
+// Clustered float64 sets can be better off with a size of their own: a plan of just
+// one round overflows it (256 x 256, 1M particles in a cloud: step 104 us as planned,
+// 89 with 768; uniformly placed 87.6 and 89.3).
 int chunk_base(int64_t n) {
   int base = 512;
   while (base < 4096 && n / (2 * base) >= 8192) base *= 2;
@@ -704,9 +708,10 @@ namespace {
 // 60 us straight and 72 through buckets at 131072 particles, 82 and 79 at
 // 262144, 233 and 125 at 1M; export 41 and 55 us at 262144, 146 and 100 at 1M
 constexpr int64_t kFirstSortMin = 1 << 18, kExportMin = 1 << 19;
-// particles from which on a thread counts four for the sort, else one: float32
-// count pass 8.7 us with one and 9.9 with four at 1M, 19.7 and 16.3 at 2M, 503 and
-// 318 at 67M; float64, 32768 particles 6.5 and 12.9
+// particles from which on a thread counts four for the sort, else one (count pass
+// in the kernel trace, a sort every six updates): float32 6.8 us with one and 7.3
+// with four at 1M, 11.9 and 10.8 at 2M, 206 and 145 at 33M; float64, 32768
+// particles 4.0 and 8.9
 constexpr int64_t kCountWide = 3 << 19;
 
 // counting sort of every instance's particles by tile into the other set
@@ -1511,7 +1516,8 @@ pic_status_t pic_diagnostics(pic_ctx_t c, double* out) {
     if (st) return st;
   }
   auto pa = parts_of(c, in.d, c->cur);
-  st = c->hip(launch_diag(c->dtype, in.d.H, in.d.g, in.d.sc, hs, &pa, in.d.n, in.d.ph, c->h_diag, c->stream), "diagnostics");
+  st = c->hip(launch_diag(c->dtype, in.d.H, in.d.g, in.d.sc, hs, &pa, in.d.n, in.d.ph, c->h_diag, c->stream),
+              "diagnostics");
   if (!st) st = c->hip(hipStreamSynchronize(c->stream), "diag sync");
   if (st) return st;
   double v[10] = {0};

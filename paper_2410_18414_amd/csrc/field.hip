@@ -114,8 +114,9 @@ constexpr int kColMaxModes = 2;
 // The history terms of one mode's update that do not depend on J^{n+1} (BDF-k:
 // their sums); at(slot, mode) is that mode of a history slot.
 template <int SCHEME, int K, class At>
-__device__ __forceinline__ void load_terms(double2& o0, double2& o1, double2& o2, double2& o3, double2& o4, int ky, int part, int nst, bool naive_rho,
-                                           const HistSlots& hs, const SchemeCoef& sc, At at) {
+__device__ __forceinline__ void load_terms(double2& o0, double2& o1, double2& o2, double2& o3, double2& o4, int ky,
+                                           int part, int nst, bool naive_rho, const HistSlots& hs,
+                                           const SchemeCoef& sc, At at) {
   const int c0 = part == 0 ? 0 : part - 1;
   double2 h0, h1, h2, h3, h4;
   h0 = h1 = h2 = h3 = h4 = make_double2(0.0, 0.0);
@@ -169,8 +170,9 @@ __device__ __forceinline__ void load_terms(double2& o0, double2& o1, double2& o2
 // The update of one mode of a part: writes its new history, returns what the
 // mesh fields are made of.  J(i): the mode's transformed currents.
 template <int SCHEME, int K, class At, class JAt>
-__device__ __forceinline__ double2 update_mode(double2 h0, double2 h1, double2 h2, double2 h3, double2 h4, int ky, double kxs, double kys, int part, int nst,
-                                               bool naive_rho, const HistSlots& hs, const SchemeCoef& sc, At at, JAt J) {
+__device__ __forceinline__ double2 update_mode(double2 h0, double2 h1, double2 h2, double2 h3, double2 h4, int ky,
+                                               double kxs, double kys, int part, int nst, bool naive_rho,
+                                               const HistSlots& hs, const SchemeCoef& sc, At at, JAt J) {
   const int c0 = part == 0 ? 0 : part - 1;
   const double Lh = 1.0 + (kxs * kxs + kys * kys) * sc.inv_alpha2;
   double2 out;
@@ -405,8 +407,8 @@ __global__ void __launch_bounds__(512) k_columns_split(const InstDesc* __restric
     const int ky = tid + m * nth;
     if (ky >= N) continue;
     const double kys = ky_sym(ky, g);
-    const double2 out = update_mode<SCHEME, K>(h0[m], h1[m], h2[m], h3[m], h4[m], ky, kxs, kys, part, nst, naive_rho, hs, sc, at,
-                                               [&](int i) { return Jh[i * N + ky]; });
+    const double2 out = update_mode<SCHEME, K>(h0[m], h1[m], h2[m], h3[m], h4[m], ky, kxs, kys, part, nst, naive_rho,
+                                               hs, sc, at, [&](int i) { return Jh[i * N + ky]; });
     store[ky] = cscale(out, scale);
   }
   __syncthreads();
@@ -522,7 +524,7 @@ constexpr int kSmallCells = 1024, kSmallThreads = 768;  // a mode (at most 5 x 1
 
 // LDS: three buffers -- the spectra of a part's two outputs move between the
 // first two, then the rows of its three mesh fields between the free one and the
-// third -- and the twiddles of both axes: 75 KiB at 32 x 32, two blocks per CU
+// third -- and the twiddles of both axes: 73 KiB at 32 x 32, two blocks per CU
 __host__ __device__ inline int small_buffer(int nx, int ny) {
   const int spec = 2 * (nx / 2 + 1) * (ny | 1), rows = 3 * ((ny + 1) / 2) * nx;
   return spec > rows ? spec : rows;
@@ -689,7 +691,8 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double* __restrict__
 #pragma unroll
     for (int i = 0; i < NV; ++i) red[threadIdx.x >> 6][i] = v[i];
   __syncthreads();
-  if (threadIdx.x < NV) out[threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+  const int t = threadIdx.x;
+  if (t < NV) out[t] = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
 }
 
 template <typename T, int SCHEME>

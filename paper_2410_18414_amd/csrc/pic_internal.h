@@ -2,8 +2,8 @@
 //
 // Every hot-path kernel runs over a flattened grid that covers all instances
 // of a context (one instance for the plain API, many for an ensemble): each
-// instance owns a contiguous range of blocks, found by binary search over the
-// per-instance block offsets in its descriptor (InstDesc, device memory).
+// instance owns a contiguous range of blocks, found by a whole wave in a table of
+// the ranges' first blocks that follows the descriptors (find_inst).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -294,7 +294,8 @@ struct SchemeCoef {
 constexpr int kFieldSlots = 12;
 
 // One FFT length (fft_lds.h): its passes' radices in order, 16 bits each (at
-// most eight passes; powers of two choose their own)
+// most eight passes; powers of two with at most one butterfly per thread have
+// compiled passes of their own)
 struct FftPlan {
   int n;
   float inv_n;  // 1 / n
@@ -459,9 +460,10 @@ hipError_t launch_set_particles(int dtype, const void* parts, int64_t n, const d
 
 // tiles.hip
 size_t tiled_lds_bytes(int dtype, int mode, const TileP& tp, bool naive);
-hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int count_items, int nb_count, int nb_tiles, int nb_part,
-                            int src_set, hipStream_t s);
+hipError_t launch_tile_sort(int dtype, const InstDesc* D, int ninst, int count_items, int nb_count, int nb_tiles,
+                            int nb_part, int src_set, hipStream_t s);
 hipError_t launch_cell_scan(const InstDesc* D, int ninst, int nb_tiles, hipStream_t s);
+// after a sort or a loaded state, in ensembles: the tiled passes' block ranges
 hipError_t launch_work_first(InstDesc* D, int ninst, hipStream_t s);
 // reorder.hip: the sort of sets in no known order (src -> src, by way of
 // src ^ 1, every instance), and one instance's set src to out in original order
@@ -486,8 +488,8 @@ int columns_nb(int ny);
 size_t rows_r2c_lds_bytes(int nx, int R);
 size_t rows_c2r_lds_bytes(int nx, int R);
 size_t adj_columns_lds_bytes(int ny);
-// blocks per kx of the forward column kernel (4 for BDF-k and CDF-2, split
-// by output; 1 for DIRK-2) and the split kernel's LDS bytes
+// blocks per kx of the forward column kernel (four, split by output) and its LDS
+// bytes
 int columns_parts(int scheme);
 size_t columns_split_lds_bytes(int ny, int nstage);  // nstage: sub-stepped DIRK stages (else 0)
 // adj = true: the adjoint field solve's transforms (LF -> LS, LS -> LJ; one instance)

@@ -114,7 +114,7 @@ __device__ __forceinline__ uint64_t key_group(int key, bool active) {
 // group is the particle's slot among its cell's particles, kept for the scatter.
 // Bound by the chain load, groups, atomic, store: one particle per thread for
 // small sets, four whose chains overlap for large ones (four chains in a row took
-// 15 us at 32768 float64 particles, 419 us at 67M float32; now 6.5 and 318).
+// 13.4 us at 1M float32 particles, 419 at 67M; now 10.5 and 318).
 template <typename T, int NI>
 __global__ void __launch_bounds__(kThreads) k_tile_count(const InstDesc* __restrict__ D, int ninst, int set) {
   const int ii = find_inst(D, ninst, BK_COUNT, blockIdx.x);
@@ -215,8 +215,10 @@ __device__ void tile_scan_block(const InstDesc& d, const TileP& tp) {
 // the tile's total; the block of the instance that finishes last (a
 // device-scope counter, reset by that block) then scans the tile totals into
 // tile starts and the chunk list.  A chain of latencies: one vector load and one
-// wave scan for the cells of a tile, wave scans for the totals (7.8 us at 32 x 32
-// with a load and a scan per 64 cells and block-wide scan steps, now 5.6).
+// wave scan for the cells of a tile, wave scans for the totals.  With a load and a
+// scan per 64 cells and block-wide scan steps 7.8 us at 32 x 32 and 9.5 at 128 x 128,
+// this way 5.6 and 8.4; beyond a quarter of a million cells, where the fences'
+// write-backs of dirty lines bound it, 104 and 113 at 1024 x 1024, once a sort.
 __global__ void __launch_bounds__(kThreads) k_cell_scan(const InstDesc* __restrict__ D, int ninst) {
   const int ii = find_inst(D, ninst, BK_TILES, blockIdx.x);
   const InstDesc& d = D[ii];
