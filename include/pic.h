@@ -158,7 +158,7 @@ typedef struct {                /* [host] */
                                    largest power of two not above nx and ny); a side
                                    that is no multiple of it ends in a partial tile     */
   int32_t chunk;                /* particles per workgroup of the sorted passes, at most
-                                   (64..65536); 0 = from max_particles, the grid and the
+                                   (64..65536); 0 = from the particles loaded, the grid and the
                                    precision                                             */
   int32_t slack;                /* cells a particle may drift from its tile and still use
                                    the tile's LDS window (1..8); 0 = default (3); at

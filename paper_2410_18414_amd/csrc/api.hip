@@ -204,14 +204,15 @@ int chunk_base(int64_t n) {
   while (base < 4096 && n / (2 * base) >= 8192) base *= 2;
   return base;
 }
-// The tiles of a plan by extent (full, and partial at the high edges): how many,
-// their expected particles, and those with four standard deviations of margin
+// The tiles of a plan for n particles by extent (full, and partial at the high
+// edges): how many, their expected particles, and those with four standard
+// deviations of margin
 struct TileKind {
   double count, mean, most;
 };
-std::array<TileKind, 4> tile_kinds(const pic_config_t& c, const TileP& t) {
+std::array<TileKind, 4> tile_kinds(const pic_config_t& c, const TileP& t, int64_t n) {
   const int fx = c.nx / t.ts, fy = c.ny / t.ts, rx = c.nx - fx * t.ts, ry = c.ny - fy * t.ts;
-  const double per_cell = (double)c.max_particles / ((double)c.nx * c.ny);
+  const double per_cell = (double)n / ((double)c.nx * c.ny);
   auto kind = [&](int count, int w, int h) {
     const double k = per_cell * w * h;
     return TileKind{(double)count, k, k + 4.0 * std::sqrt(k)};
@@ -219,15 +220,14 @@ std::array<TileKind, 4> tile_kinds(const pic_config_t& c, const TileP& t) {
   return {kind(fx * fy, t.ts, t.ts), kind(rx ? fy : 0, rx, t.ts), kind(ry ? fx : 0, ry, t.ts),
           kind(rx && ry ? 1 : 0, rx, ry)};
 }
-int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
-  const int64_t n = c.max_particles;
+int plan_chunk(const pic_config_t& c, const TileP& t, int64_t n, int64_t total) {
   const int base = chunk_base(n);
   const bool f32 = c.particle_dtype == PIC_F32;
   if (n <= 8192 && total <= 128 * 256) return 128;
   const size_t lds = tiled_lds_bytes(c.particle_dtype, 2, t, (c.flags & PIC_FLAG_NAIVE_RHO) != 0);
   const double per_cu = (double)std::max<size_t>(1, std::min<size_t>(4, 163840 / lds));
   const double slots = 256.0 * per_cu * ((double)n / (double)total);
-  const auto tiles = tile_kinds(c, t);
+  const auto tiles = tile_kinds(c, t, n);
   const double fixed = f32 ? 1.2 : 2.2;
   int best = base;
   double best_cost = 1e300;
@@ -260,8 +260,8 @@ int plan_chunk(const pic_config_t& c, const TileP& t, int64_t total) {
 }
 
 // Tile plan: tiles of 16x16 cells (smaller on small grids), a slack of three
-// cells, chunks by plan_chunk, unless the config sets them.  total: the
-// capacity of all instances of the context.
+// cells, chunks by plan_chunk for the capacity, unless the config sets them.
+// total: the capacity of all instances of the context.
 TileP plan_tiles(const pic_config_t& c, int64_t total) {
   TileP t{};
   t.nx = c.nx;
@@ -288,7 +288,7 @@ TileP plan_tiles(const pic_config_t& c, int64_t total) {
     t.row_lanes <<= 1;
     t.log_row_lanes += 1;
   }
-  t.chunk = c.chunk ? c.chunk : plan_chunk(c, t, total);
+  t.chunk = c.chunk ? c.chunk : plan_chunk(c, t, c.max_particles, total);
   t.max_work = t.ntiles + ceil_div(c.max_particles, t.chunk);
   t.log_group = 0;
   while ((t.ntiles - 1) >> t.log_group >= kMaxBuckets) t.log_group++;
@@ -446,6 +446,8 @@ struct Instance {
   Layout L{};
   size_t off = 0;  // byte offset of the instance region in the workspace
   InstDesc d{};    // host copy of the device descriptor
+  bool loaded = false;
+  int64_t planned = 0;  // particles the chunk size is planned for
 };
 
 }  // namespace
@@ -576,6 +578,7 @@ struct pic_ctx_s {
   size_t lds_r2c = 0, lds_c2r = 0, lds_col = 0, lds_small = 0, lds_adj_col = 0, lds_tiled[3] = {0, 0, 0};
   int max_ny = 0;  // largest grid side in y over the instances (column kernel block size)
   int dtype = 0, degree = 3, scheme = 0;
+  bool replanned = false;  // the chunk sizes have been planned for loaded particles
   int split_items = 0;  // particles per thread of the bucket split (first sort)
   int count_items = 0;  // particles per thread of the tile count
   int geo = 0;  // compiled window geometry shared by every instance (0: none, runtime geometry)
@@ -799,6 +802,32 @@ pic_status_t do_solve(pic_ctx_t c) {
   return PIC_OK;
 }
 
+// Chunk sizes for the particles loaded, where those are not the capacity the context
+// was planned for (an eighth of it, 128 x 128 and 1M float64 particles: a step of 119
+// us with the capacity's chunks, 78 as planned anew).  A smaller chunk has
+// to leave the chunk list (max_work) long enough.  An ensemble is planned when every
+// instance is loaded; after that each instance as its count changes.  The sort reads
+// the size; the caller uploads it.
+void plan_loaded(pic_ctx_t c) {
+  int64_t total = 0;
+  bool same = true;
+  for (const Instance& in : c->inst) {
+    if (!in.loaded) return;
+    total += in.d.n;
+    same = same && in.planned == in.d.n;
+  }
+  if (same) return;
+  for (Instance& in : c->inst) {
+    if (c->replanned && in.planned == in.d.n) continue;
+    in.planned = in.d.n;
+    if (in.cfg.chunk) continue;
+    const int64_t n = std::max<int64_t>(in.d.n, 1), room = in.d.tp.max_work - in.d.tp.ntiles;
+    const int64_t least = (n + room - 1) / room;
+    in.d.tp.chunk = (int)std::max<int64_t>(plan_chunk(in.cfg, in.d.tp, n, std::max<int64_t>(total, 1)), least);
+  }
+  c->replanned = true;
+}
+
 pic_status_t reset_fields(pic_ctx_t c, Instance& in) {
   const InstDesc& d = in.d;
   pic_status_t st = c->hip(launch_fill_f64((double*)d.H, (size_t)c->hist.nslots * in.L.plane_c * 2, 0.0, c->stream),
@@ -944,6 +973,7 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     Instance& in = c->inst[i];
     const pic_config_t& cf = cfgs[i];
     in.cfg = cf;
+    in.planned = cf.max_particles;
     in.L = plan_instance(cf, cap);
     in.off = off;
     off += in.L.total;
@@ -1365,6 +1395,8 @@ pic_status_t init_particles(pic_ctx_t c, int64_t n, const double* x, const doubl
     if (st) return st;
   }
   in.d.n = n;
+  in.loaded = true;
+  plan_loaded(c);
   st = c->upload_desc();
   if (st) return st;
   if (in.cfg.sort_interval == 0 && n > 0) {
@@ -1781,7 +1813,9 @@ pic_status_t pic_load_state_h(pic_ctx_t c, const void* src, const int64_t* heade
   for (int i = 0; i < ni; ++i) {
     counts_changed = counts_changed || c->inst[i].d.n != ns[i];
     c->inst[i].d.n = ns[i];
+    c->inst[i].loaded = true;
   }
+  if (counts_changed) plan_loaded(c);
   c->nupd = h[2];
   c->vflip = (int)h[3];
   c->cur = cur;
