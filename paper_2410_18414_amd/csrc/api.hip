@@ -343,7 +343,7 @@ Layout plan_instance(const pic_config_t& c, int64_t total) {
   L.twork = take((size_t)tp.max_work * 16);
   L.tnwork = take(4);
   L.tdone = take(8);  // and InstDesc::jread
-  L.tbucket = take((size_t)2 * kMaxBuckets * 4);  // cleared together with those
+  L.tbucket = take((size_t)2 * kMaxBuckets * 4);  // cleared together with the two above
   L.trank = take((size_t)cap * 4);
   if (c.flags & PIC_FLAG_ADJOINT) {
     L.LF = take(11 * plane_r * 8);
@@ -1103,7 +1103,8 @@ pic_status_t create(const pic_config_t* cfgs, int ninst, void* workspace, size_t
     }
     if (e == hipSuccess) e = hipMemset(d.tb.count, 0, (size_t)d.tp.ntiles * 4);
     if (e == hipSuccess) e = hipMemset(d.tb.ccount, 0, (size_t)d.tp.ntiles * d.tp.ts * d.tp.ts * 4);
-    if (e == hipSuccess) e = hipMemset(d.tb.done, 0, (char*)(d.tb.bcount + kMaxBuckets) - (char*)d.tb.done);
+    // chunks in use, blocks of the scan and of the solve, bucket counters
+    if (e == hipSuccess) e = hipMemset(d.tb.nwork, 0, (char*)(d.tb.bcount + kMaxBuckets) - (char*)d.tb.nwork);
   }
   c->sort_every = every;
   c->geo = tiled_geometry(c->inst[0].d.tp);
